@@ -85,8 +85,11 @@ __global__ void k_fill(int *__restrict__ p, int value, int64_t count)
         p[i] = value;
 }
 
-constexpr int kCellidPer = 4;                 // particles per thread
-constexpr int kCellidBlock = kBlock * kCellidPer;  // 1024 particles per block
+// Particles per thread of the histogram pass: one up to kCellidSmall particles
+// (a block of 1024 then serializes four rounds on one CU while others idle:
+// 32,768 particles 13.6 us at four per thread), else four (fewer global atomics).
+constexpr int kCellidPer = 4;
+constexpr int64_t kCellidSmall = 1 << 18;
 
 __device__ __forceinline__ int particle_cell(const Batch &B, int i, int *status)
 {
@@ -136,7 +139,7 @@ __device__ __forceinline__ int particle_cell(const Batch &B, int i, int *status)
 constexpr int kPeelMax = 8;    // lane groups of one cell served per wavefront pass
 constexpr int kPeelGroup = 4;  // ... while the groups found hold at least this many lanes
 
-// Cell ids and the histogram.  A block takes 1024 particles and first counts
+// Cell ids and the histogram.  A block takes 256 kPer particles and first counts
 // them per cell in an LDS hash table, then adds each distinct cell's count to
 // the global histogram with one atomic; a particle's arrival rank is its
 // block's base plus its rank inside the block (ranks are unordered; the
@@ -146,34 +149,29 @@ constexpr int kPeelGroup = 4;  // ... while the groups found hold at least this 
 // one ballot and served by a single pair of LDS atomics for the whole group,
 // repeated while such groups are large; the remaining lanes go one by one.
 //
-// With an activity mask (kMasked; flag and tcount cleared) the pass also
-// leaves in flag[cell] the largest activity value of the cell's particles (1,
-// or 2 for cells cut into finer work items; 0: no active particle) and in
-// tcount[cell] the number of its active particles.  A block keeps both in one
-// LDS word per cell: the active count in the low kActShift bits, the count of
-// those with value 2 above them (at most kCellidBlock each).
-constexpr int kActShift = 20;
-template <bool kMasked>
+// With an activity mask (kMasked; tcount cleared) the pass also leaves in
+// tcount[cell] the number of the cell's active particles.
+template <bool kMasked, int kPer>
 __global__ __launch_bounds__(kBlock) void k_cellid(Batch B, int *__restrict__ cid,
                                                    int *__restrict__ slot,
                                                    int *__restrict__ count, int *__restrict__ status,
-                                                   int *__restrict__ flag, int *__restrict__ tcount)
+                                                   int *__restrict__ tcount)
 {
     __shared__ int hkey[kHash];
     __shared__ int hcnt[kHash];
-    __shared__ int hflag[kMasked ? kHash : 1];
+    __shared__ int hact[kMasked ? kHash : 1];
     for (int h = threadIdx.x; h < kHash; h += kBlock) {
         hkey[h] = -1;
         hcnt[h] = 0;
         if (kMasked)
-            hflag[h] = 0;
+            hact[h] = 0;
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    int hs[kCellidPer], rk[kCellidPer], act[kCellidPer];
-    const int base = blockIdx.x * kCellidBlock;
+    int hs[kPer], rk[kPer], act[kPer];
+    const int base = blockIdx.x * kBlock * kPer;
 #pragma unroll
-    for (int k = 0; k < kCellidPer; ++k) {
+    for (int k = 0; k < kPer; ++k) {
         const int i = base + k * kBlock + threadIdx.x;
         const bool valid = i < B.ntot;
         int id = -1;
@@ -190,7 +188,6 @@ __global__ __launch_bounds__(kBlock) void k_cellid(Batch B, int *__restrict__ ci
         rk[k] = 0;
         unsigned long long rem = __ballot(valid);
         const unsigned long long act_b = kMasked ? __ballot(act[k] > 0) : 0ull;
-        const unsigned long long fine_b = kMasked ? __ballot(act[k] == 2) : 0ull;
         for (int it = 0; it < kPeelMax && rem; ++it) {
             const int leader = __ffsll((long long)rem) - 1;
             const int key = __builtin_amdgcn_readlane(id, leader);
@@ -201,8 +198,7 @@ __global__ __launch_bounds__(kBlock) void k_cellid(Batch B, int *__restrict__ ci
                 hh = lds_hash_slot(hkey, key);
                 hb = atomicAdd(&hcnt[hh], gsize);
                 if (kMasked && (act_b & grp))
-                    atomicAdd(&hflag[hh], __popcll(act_b & grp) +
-                                              (__popcll(fine_b & grp) << kActShift));
+                    atomicAdd(&hact[hh], __popcll(act_b & grp));
             }
             hh = __builtin_amdgcn_readlane(hh, leader);
             hb = __builtin_amdgcn_readlane(hb, leader);
@@ -220,23 +216,21 @@ __global__ __launch_bounds__(kBlock) void k_cellid(Batch B, int *__restrict__ ci
             hs[k] = h;
             rk[k] = atomicAdd(&hcnt[h], 1);
             if (kMasked && act[k] > 0)
-                atomicAdd(&hflag[h], act[k] == 2 ? 1 + (1 << kActShift) : 1);
+                atomicAdd(&hact[h], 1);
         }
     }
     __syncthreads();
     for (int h = threadIdx.x; h < kHash; h += kBlock) {
         const int c = hcnt[h];
         if (c > 0) {
-            if (kMasked && hflag[h] > 0) {
-                atomicMax(&flag[hkey[h]], (hflag[h] >> kActShift) > 0 ? 2 : 1);
-                atomicAdd(&tcount[hkey[h]], hflag[h] & ((1 << kActShift) - 1));
-            }
+            if (kMasked && hact[h] > 0)
+                atomicAdd(&tcount[hkey[h]], hact[h]);
             hcnt[h] = atomicAdd(&count[hkey[h]], c);  // becomes the block's base
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kCellidPer; ++k) {
+    for (int k = 0; k < kPer; ++k) {
         const int i = base + k * kBlock + threadIdx.x;
         if (hs[k] >= 0)
             slot[i] = hcnt[hs[k]] + rk[k];
@@ -279,6 +273,42 @@ __global__ __launch_bounds__(kBlock) void k_scan_up(const int *__restrict__ in, 
     }
     if (threadIdx.x == 0)
         *done = 0;
+}
+
+// The whole scan by one block, for m <= kScanOne: one launch instead of two
+// (on 1,000 cells 3 us instead of 7).
+constexpr int kScanThreads = 1024;
+constexpr int kScanOne = kScanThreads * kScanItems;
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(const int *__restrict__ in, int m,
+                                                           int *__restrict__ out)
+{
+    __shared__ int sh[kScanThreads / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // as many entries per thread as m needs
+    const int per = (m + kScanThreads - 1) / kScanThreads;
+    const int base = threadIdx.x * per;
+    int v[kScanItems];
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        v[k] = k < per && base + k < m ? in[base + k] : 0;
+        s += v[k];
+    }
+    const int inc = wave_inclusive_scan(s, lane);
+    if (lane == 63)
+        sh[wid] = inc;
+    __syncthreads();
+    int run = inc - s;
+    for (int w = 0; w < wid; ++w)
+        run += sh[w];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        if (k < per && base + k < m)
+            out[base + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == kScanThreads - 1)
+        out[m] = run;
 }
 
 __global__ __launch_bounds__(kBlock) void k_scan_down(const int *__restrict__ in, int m,
@@ -327,12 +357,12 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int *__restrict__ cid,
 }
 
 // Masked passes: a cell is binned when its stencil (x +-hx, y and z +-1,
-// periodic: masked passes run in split coordinates) reaches a cell flagged
-// active (flag[c] > 0, left by k_cellid); the counts of the others are set to
-// zero before the scan, so those cells stay empty.  The cells a target's
+// periodic: masked passes run in split coordinates) reaches a cell with an
+// active particle (tcount, left by k_cellid); the counts of the others are set
+// to zero before the scan, so those cells stay empty.  The cells a target's
 // stencil reaches are all binned, in the order a full pass gives them, so the
 // sums are those of the full pass.
-__global__ __launch_bounds__(kBlock) void k_relevant(Geom g, const int *__restrict__ flag,
+__global__ __launch_bounds__(kBlock) void k_relevant(Geom g, const int *__restrict__ tcount,
                                                      int *__restrict__ count)
 {
     const int c = blockIdx.x * kBlock + threadIdx.x;
@@ -352,7 +382,7 @@ __global__ __launch_bounds__(kBlock) void k_relevant(Geom g, const int *__restri
             for (int dx = -g.hx; dx <= g.hx; ++dx) {
                 int nx = cx + dx;
                 nx = nx < 0 ? nx + g.nc[0] : (nx >= g.nc[0] ? nx - g.nc[0] : nx);
-                if (flag[row + nx] > 0)
+                if (tcount[row + nx] > 0)
                     return;
             }
         }
@@ -394,13 +424,21 @@ __device__ __forceinline__ float4 gather_one(const BoxDesc &d, int v)
 
 // Sorted copy by scattering in input order: sorted[inv[i]] = particle i.
 // Reads are coalesced; writes land in runs wherever the input keeps
-// neighbours together.  Also flags boxes whose masses are not all equal.
+// neighbours together.  Also flags boxes whose masses are not all equal, and
+// leaves what the work items need: thread c also writes the stencil size of
+// cell c to src (when given) and adds the cell's target-source pairs to its
+// box's total when the box cuts its chunks.
 __global__ __launch_bounds__(kBlock) void k_gather(Batch B, const int *__restrict__ inv,
                                                    float4 *__restrict__ sorted,
                                                    int *__restrict__ mass_mixed,
                                                    const int *__restrict__ cid,
-                                                   const int *__restrict__ offsets)
+                                                   const int *__restrict__ offsets,
+                                                   const int *__restrict__ tcount,
+                                                   int *__restrict__ src,
+                                                   unsigned long long *__restrict__ work)
 {
+    __shared__ unsigned long long wave_work[kBlock / 64];
+    __shared__ int wave_box[kBlock / 64];
     const int i = blockIdx.x * kBlock + threadIdx.x;
     bool mixed = false;
     int box = 0;
@@ -423,6 +461,47 @@ __global__ __launch_bounds__(kBlock) void k_gather(Batch B, const int *__restric
         const int lane = threadIdx.x & 63;
         if (mixed && (box != b0 || lane == first))
             atomicOr(&mass_mixed[box], 1);
+    }
+    if (!src || (int)(blockIdx.x * kBlock) >= B.ctot)
+        return;
+    unsigned long long pairs = 0ull;
+    int cbox = -1;
+    if (i < B.ctot) {
+        cbox = find_box(B.cstart, B.nb, i);
+        const BoxDesc &d = box_at(B, cbox);
+        const int len = tcount ? tcount[i] : offsets[i + 1] - offsets[i];
+        const int s = len > 0 ? cell_stencil(d, offsets, i) : 0;
+        src[i] = s;
+        if (tcount || box_splits(d.n))
+            pairs = (unsigned long long)len * (unsigned)s;
+    }
+    // one atomic per block of cells of one box, else one per lane
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b0 = __builtin_amdgcn_readfirstlane(cbox);
+    const bool one = __all(cbox == b0 || cbox < 0);
+    if (one) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            pairs += __shfl_xor(pairs, o, 64);
+    } else if (pairs) {
+        atomicAdd(&work[cbox], pairs);
+    }
+    if (lane == 0) {
+        wave_work[w] = one ? pairs : 0ull;
+        wave_box[w] = one ? b0 : -1;
+    }
+    __syncthreads();
+    if (threadIdx.x < kBlock / 64 && wave_work[threadIdx.x]) {
+        // the first wavefront of each box adds the sums of all of them
+        unsigned long long sum = 0ull;
+        bool first = true;
+        for (int k = 0; k < kBlock / 64; ++k) {
+            const bool same = wave_work[k] && wave_box[k] == wave_box[threadIdx.x];
+            first = first && !(same && k < (int)threadIdx.x);
+            sum += same ? wave_work[k] : 0ull;
+        }
+        if (first)
+            atomicAdd(&work[wave_box[threadIdx.x]], sum);
     }
 }
 
@@ -561,17 +640,13 @@ __device__ void sort_cell(int cell, int b, int len, int *__restrict__ perm, int 
 // One wavefront per group of kSegGroup consecutive cells.  When the group
 // holds at most 64 particles, each lane takes one slot and ranks its index
 // among the smaller indices of the same cell (one pass for the whole group);
-// otherwise the cells are sorted one after the other.  With an activity mask
-// (chunk_count and tcount), the pass also counts the force work items of
-// each cell (mesh_chunks_for).
+// otherwise the cells are sorted one after the other.
 // Indices are compared as the signed keys k_scatter wrote.
 __global__ __launch_bounds__(kBlock) void k_segsort(Batch B, const int *__restrict__ offsets,
                                                     int *__restrict__ perm,
                                                     int *__restrict__ large_list,
                                                     int *__restrict__ large_count,
-                                                    int *__restrict__ inv,
-                                                    int *__restrict__ chunk_count,
-                                                    const int *__restrict__ tcount)
+                                                    int *__restrict__ inv)
 {
     __shared__ int buf[kBlock / 64][kLargeCell];
     const int lane = threadIdx.x & 63;
@@ -580,15 +655,6 @@ __global__ __launch_bounds__(kBlock) void k_segsort(Batch B, const int *__restri
     if (c0 >= B.ctot)
         return;
     const int nc = B.ctot - c0 < kSegGroup ? B.ctot - c0 : kSegGroup;
-    if (chunk_count && tcount && lane < nc) {
-        // with an activity mask only the cell's na active particles (sorted
-        // first) are targets: cells without one get no item, those flagged 2
-        // are marked kFineFlag and cut by k_items (k_cellid left the flags in
-        // chunk_count, the counts in tcount)
-        const int c = c0 + lane;
-        const int f = chunk_count[c], na = tcount[c];
-        chunk_count[c] = f == 0 ? 0 : (f >= 2 ? kFineFlag : mesh_chunks(na));
-    }
     int bounds[kSegGroup + 1];
 #pragma unroll
     for (int k = 0; k <= kSegGroup; ++k)
@@ -1043,6 +1109,10 @@ int scan_enqueue(sr_ctx *ctx, const int *in, int m, int *part, int *out, int *fl
 {
     if (m <= 0)
         return fill_enqueue(ctx, out, 0, 1);
+    if (m <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, ctx->stream, in, m, out);
+        return sr_check_launch(ctx, "scan");
+    }
     int tiles = (m + kScanTile - 1) / kScanTile;
     hipLaunchKernelGGL(k_scan_up, dim3(tiles), dim3(kBlock), 0, ctx->stream, in, m, part, tiles,
                        flag);
@@ -1082,10 +1152,12 @@ void bin_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, BinScratch &s)
     s.large_list = b.take<int>((size_t)large_class_base((int64_t)nn, kLargeClasses));
     s.large_count = b.take<int>(kLargeClasses + 1);
     s.mass_mixed = b.take<int>((size_t)(nb > 0 ? nb : 1));
-    s.scan_flag = b.take<int>(1);
     s.lpt = b.take<int>(64);
-    s.n_items = b.take<int>(1);
-    s.n_heads = b.take<int>(1);
+    s.counters = b.take<int>(kCounters);
+    s.work = b.take<unsigned long long>((size_t)(nb > 0 ? nb : 1));
+    s.scan_flag = s.counters;
+    s.n_items = s.counters ? s.counters + 1 : nullptr;
+    s.n_heads = s.counters ? s.counters + 2 : nullptr;
     s.vtmp = s.ktmp = s.hist = s.hist_part = nullptr;
     if (ntot >= kRadixMinN) {
         const int64_t m = (int64_t)kRadixBins * ((ntot + kRadixTile - 1) / kRadixTile);
@@ -1138,11 +1210,11 @@ static int radix_bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, i
     return sr_check_launch(ctx, "k_key_offsets");
 }
 
-// Enqueue the whole binning pass.  sorted and chunk_count may be NULL (then
-// no gather and no item counts); tcount (per-cell active counts) is given
-// exactly when the pass carries an activity mask.
+// Enqueue the whole binning pass.  sorted may be NULL (then no gather); tcount
+// (receives the per-cell active counts) is given exactly when the pass carries
+// an activity mask; items: leave stencil sizes (count) and pair totals (work).
 int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, int *perm,
-                float4 *sorted, int *chunk_count, int *tcount)
+                float4 *sorted, int *tcount, bool items)
 {
     int rc;
     {
@@ -1153,55 +1225,50 @@ int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, 
         cl.n[1] = kLargeClasses + 1;
         cl.p[2] = s.mass_mixed;
         cl.n[2] = B.nb;
-        cl.p[3] = s.scan_flag;
-        cl.n[3] = 1;
-        cl.p[4] = s.lpt;
-        cl.n[4] = 64;
-        cl.p[5] = s.n_items;
-        cl.n[5] = 1;
-        cl.p[6] = s.n_heads;
-        cl.n[6] = 1;
+        cl.p[3] = s.lpt;
+        cl.n[3] = 64;
+        cl.p[4] = s.counters;
+        cl.n[4] = kCounters;
+        cl.p[5] = tcount;
+        cl.n[5] = B.ctot;
+        cl.p[6] = reinterpret_cast<int *>(s.work);
+        cl.n[6] = 2 * B.nb;
         if ((rc = clear_enqueue(ctx, cl)))
             return rc;
     }
     const int n = B.ntot;
-    // only single-box passes carry an activity mask (the batched forms pass
-    // none); its cell flags go to chunk_count and its active counts to
-    // tcount, which k_segsort then turns into item counts
+    // only single-box passes carry an activity mask (the batched forms pass none)
     const bool masked = !B.boxes && B.one.active != nullptr;
-    if (masked && !(chunk_count && tcount))
-        return sr_fail(ctx, SR_EINVAL, "an activity mask needs item and target counts");
-    if (masked && ((rc = fill_enqueue(ctx, chunk_count, 0, B.ctot)) ||
-                   (rc = fill_enqueue(ctx, tcount, 0, B.ctot))))
-        return rc;
+    if (masked && !tcount)
+        return sr_fail(ctx, SR_EINVAL, "an activity mask needs target counts");
     // the arrival ranks are not needed once the cells are sorted: their
     // buffer takes the inverse permutation
     int *inv = sorted ? s.slot : nullptr;
+    // threads of the gather: one per particle, and per cell where items follow
+    const int64_t span = items && B.ctot > n ? B.ctot : n;
     if (!masked && s.vtmp && n >= kRadixMinN) {
         if ((rc = radix_bin_enqueue(ctx, B, s, offsets, perm, inv)))
             return rc;
         if (sorted) {
-            hipLaunchKernelGGL(k_gather, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0,
-                               ctx->stream, B, inv, sorted, s.mass_mixed, nullptr, nullptr);
+            hipLaunchKernelGGL(k_gather, dim3(blocks_for(span, kBlock)), dim3(kBlock), 0,
+                               ctx->stream, B, inv, sorted, s.mass_mixed, nullptr, offsets,
+                               nullptr, items ? s.count : nullptr, s.work);
             if ((rc = sr_check_launch(ctx, "k_gather")))
                 return rc;
         }
         return SR_OK;
     }
     if (n > 0) {
-        if (masked)
-            hipLaunchKernelGGL(k_cellid<true>, dim3(blocks_for(n, kCellidBlock)), dim3(kBlock), 0,
-                               ctx->stream, B, s.cid, s.slot, s.count, ctx->status, chunk_count,
-                               tcount);
-        else
-            hipLaunchKernelGGL(k_cellid<false>, dim3(blocks_for(n, kCellidBlock)), dim3(kBlock),
-                               0, ctx->stream, B, s.cid, s.slot, s.count, ctx->status, nullptr,
-                               nullptr);
+        const int per = n <= kCellidSmall ? 1 : kCellidPer;
+        const auto kern = masked ? (per == 1 ? k_cellid<true, 1> : k_cellid<true, kCellidPer>)
+                                 : (per == 1 ? k_cellid<false, 1> : k_cellid<false, kCellidPer>);
+        hipLaunchKernelGGL(kern, dim3(blocks_for(n, kBlock * per)), dim3(kBlock), 0, ctx->stream,
+                           B, s.cid, s.slot, s.count, ctx->status, masked ? tcount : nullptr);
         if ((rc = sr_check_launch(ctx, "k_cellid")))
             return rc;
         if (masked) {
             hipLaunchKernelGGL(k_relevant, dim3(blocks_for(B.ctot, kBlock)), dim3(kBlock), 0,
-                               ctx->stream, B.one.g, chunk_count, s.count);
+                               ctx->stream, B.one.g, tcount, s.count);
             if ((rc = sr_check_launch(ctx, "k_relevant")))
                 return rc;
         }
@@ -1215,8 +1282,7 @@ int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, 
             return rc;
     }
     hipLaunchKernelGGL(k_segsort, dim3(blocks_for(B.ctot, kBlock / 64 * kSegGroup)), dim3(kBlock), 0,
-                       ctx->stream, B, offsets, perm, s.large_list, s.large_count, inv,
-                       masked ? chunk_count : nullptr, masked ? tcount : nullptr);
+                       ctx->stream, B, offsets, perm, s.large_list, s.large_count, inv);
     if ((rc = sr_check_launch(ctx, "k_segsort")))
         return rc;
     if (n > kLargeCell) {
@@ -1236,9 +1302,10 @@ int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, 
             return rc;
     }
     if (sorted && n > 0) {
-        hipLaunchKernelGGL(k_gather, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, ctx->stream,
-                           B, inv, sorted, s.mass_mixed, masked ? s.cid : nullptr,
-                           masked ? offsets : nullptr);
+        hipLaunchKernelGGL(k_gather, dim3(blocks_for(span, kBlock)), dim3(kBlock), 0,
+                           ctx->stream, B, inv, sorted, s.mass_mixed, masked ? s.cid : nullptr,
+                           offsets, masked ? tcount : nullptr, items ? s.count : nullptr,
+                           s.work);
         if ((rc = sr_check_launch(ctx, "k_gather")))
             return rc;
     }
@@ -1275,7 +1342,7 @@ extern "C" int sr_bin(sr_ctx *ctx, const float *x, const float *y, const float *
         return rc;
     Bump b{ctx->arena, 0, ctx->arena_cap};
     bin_layout(b, n, B.ctot, 1, s);
-    return bin_enqueue(ctx, B, s, cell_offsets, perm, nullptr, nullptr, nullptr);
+    return bin_enqueue(ctx, B, s, cell_offsets, perm, nullptr, nullptr, false);
 }
 
 extern "C" int sr_permute(sr_ctx *ctx, const int32_t *perm, int64_t n, int32_t elem_bytes,

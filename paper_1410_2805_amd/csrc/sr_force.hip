@@ -34,157 +34,10 @@
 #include <cmath>
 
 #include "sr_internal.h"
+#include "sr_item.h"
 #include "sr_pair.h"
 
 namespace {
-
-
-// The pair loop of one work item by one wavefront (tile, st, red: LDS).
-__device__ __forceinline__ void process_item(const Batch &B, const int4 item,
-                                             const float4 *__restrict__ sorted,
-                                             const int *__restrict__ offsets,
-                                             const int *__restrict__ perm,
-                                             const int *__restrict__ mass_mixed,
-                                             const ForceParams &fp, float4 *tile, Stencil &st,
-                                             int lane, float4 *__restrict__ subsums)
-{
-    const int kb = item.y, nt = item.z, S = item_split(item), box = item_box(item);
-    const BoxDesc &d = box_at(B, box);
-    const Geom &g = d.g;
-    int cx, cy, cz;
-    decode_cell(item.x - d.cbase, g, cx, cy, cz);
-    const int cc[3] = {cx, cy, cz};
-    float F[3];
-    frame_shift(g, cc, F);
-    build_stencil(st, offsets + d.cbase, g, cx, cy, cz, F, lane);
-
-    // two targets per lane: lane t of a group holds targets t and t + ln
-    const bool two = item_two(item);
-    const int ln = two ? (nt + 1) >> 1 : nt;
-    const int part = lane_group(lane, ln);
-    const int t = lane - part * ln;
-    const bool has_target = part < S;
-    const bool has2 = two && has_target && t + ln < nt;
-    const float4 pt = sorted[kb + t];
-    const float4 pt2 = sorted[kb + (has2 ? t + ln : t)];
-    const bool pas = is_passive(pt, g);
-    const bool pas2 = is_passive(pt2, g);
-    const float xi = pt.x + F[0], yi = pt.y + F[1], zi = pt.z + F[2];
-    const float xj = pt2.x + F[0], yj = pt2.y + F[1], zj = pt2.z + F[2];
-    const bool uniform = mass_mixed[box] == 0;
-    __syncthreads();
-
-    float acx = 0.f, acy = 0.f, acz = 0.f;
-    float bcx = 0.f, bcy = 0.f, bcz = 0.f;
-    if (__any((has_target && !pas) || (has2 && !pas2))) {
-        // a sub-item takes its part [sk T / ns, (sk + 1) T / ns) of the T sources
-        const int ns = item_nsub(item), sk = item_sub(item);
-        const int all = st.pbeg[kMaxPieces];
-        const int total = ns > 1 ? (int)((long long)(sk + 1) * all / ns) : all;
-        // a pass stages `cap` sources (a multiple of the 4 S slice quantum, so
-        // that padding stays inside the tile); the next pass's sources are
-        // loaded before the current pass computes (each load waits for its
-        // image shift: deferring the shifts past the pair loop costs this
-        // kernel its occupancy step)
-        const int quantum = 4 * S;
-        const int cap = kItemTab.cap[S];
-        const int qrecip = kItemTab.qrecip[S];
-        // sources outside the cutoff of the whole box of the item's targets
-        // are dropped before they reach the tile
-        const TargetBox tb = target_box(xi, yi, zi, xj, yj, zj);
-        float4 pre[kTile / 64];
-        int p = 0;
-        int g0 = ns > 1 ? (int)((long long)sk * all / ns) : 0;
-        int cnt = total - g0 < cap ? total - g0 : cap;
-        load_tile(pre, st, sorted, g0, cnt, lane, p);
-        for (;;) {
-            // kept sources, rounded up to the quantum with entries that add zero
-            const int nq = quanta_of(store_tile_kept(tile, pre, tb, fp, lane), quantum, qrecip);
-            __syncthreads();
-            const int g1 = g0 + cnt;
-            const int cnt1 = total - g1 < cap ? total - g1 : cap;
-            if (cnt1 > 0)
-                load_tile(pre, st, sorted, g1, cnt1, lane, p);
-            const int slice = 4 * nq;
-            const float4 *src = tile + (has_target ? part : 0) * slice;
-            float tx = 0.f, ty = 0.f, tz = 0.f;
-            if (two) {
-                float ux = 0.f, uy = 0.f, uz = 0.f;
-                if (uniform)
-                    pair_tile2<true>(src, slice, xi, yi, zi, xj, yj, zj, fp, tx, ty, tz, ux, uy,
-                                     uz);
-                else
-                    pair_tile2<false>(src, slice, xi, yi, zi, xj, yj, zj, fp, tx, ty, tz, ux, uy,
-                                      uz);
-                bcx += ux;
-                bcy += uy;
-                bcz += uz;
-            } else if (uniform) {
-                pair_tile<true>(src, slice, xi, yi, zi, fp, tx, ty, tz);
-            } else {
-                pair_tile<false>(src, slice, xi, yi, zi, fp, tx, ty, tz);
-            }
-            acx += tx;
-            acy += ty;
-            acz += tz;
-            __syncthreads();
-            if (cnt1 <= 0)
-                break;
-            g0 = g1;
-            cnt = cnt1;
-        }
-        if (uniform) {
-            acx *= pt.w;
-            acy *= pt.w;
-            acz *= pt.w;
-            bcx *= pt2.w;
-            bcy *= pt2.w;
-            bcz *= pt2.w;
-        }
-    }
-    // add the S group sums of each target in group order
-    tile[lane] = make_float4(acx, acy, acz, 0.f);
-    tile[64 + lane] = make_float4(bcx, bcy, bcz, 0.f);
-    __syncthreads();
-    if (part == 0) {
-        for (int q = 1; q < S; ++q) {
-            const float4 o = tile[t + q * ln];
-            acx += o.x;
-            acy += o.y;
-            acz += o.z;
-        }
-        // sub-item 0 writes the accelerations as a whole item does, sub-item
-        // sk > 0 its partial sums to plane sk - 1
-        const int sub = item_sub(item);
-        float4 *pp = sub > 0 ? subsums + (size_t)(sub - 1) * B.ntot : nullptr;
-        if (pp) {
-            pp[kb + t] = pas ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(acx, acy, acz, 0.f);
-        } else {
-            const int orig = perm[kb + t] - d.pbase;
-            d.ax[orig] = pas ? 0.f : acx;
-            d.ay[orig] = pas ? 0.f : acy;
-            d.az[orig] = pas ? 0.f : acz;
-        }
-        if (has2) {
-            for (int q = 1; q < S; ++q) {
-                const float4 o = tile[64 + t + q * ln];
-                bcx += o.x;
-                bcy += o.y;
-                bcz += o.z;
-            }
-            if (pp) {
-                pp[kb + t + ln] =
-                    pas2 ? make_float4(0.f, 0.f, 0.f, 0.f) : make_float4(bcx, bcy, bcz, 0.f);
-            } else {
-                const int orig2 = perm[kb + t + ln] - d.pbase;
-                d.ax[orig2] = pas2 ? 0.f : bcx;
-                d.ay[orig2] = pas2 ? 0.f : bcy;
-                d.az[orig2] = pas2 ? 0.f : bcz;
-            }
-        }
-    }
-    __syncthreads();  // the tile is reused by the next item
-}
 
 // Position in the item order served by workgroup b: workgroups are dealt to
 // the 8 XCDs round-robin, and XCD k serves the chunks of 64 consecutive
@@ -200,49 +53,53 @@ __device__ __forceinline__ int item_position(int b)
 // One workgroup per item: the grid covers the chunk bound (a multiple of 512;
 // at most kMaskedGrid workgroups in masked passes), and a workgroup also
 // serves positions + k gridDim when sub-items make more items than that.
-__global__ __launch_bounds__(64) void k_force(Batch B, const int4 *__restrict__ items,
-                                              const int *__restrict__ n_items,
-                                              const float4 *__restrict__ sorted,
-                                              const int *__restrict__ offsets,
-                                              const int *__restrict__ perm,
-                                              const int *__restrict__ mass_mixed, ForceParams fp,
-                                              float4 *__restrict__ subsums)
+__global__ __launch_bounds__(64, 8) void k_force(Batch B, const int4 *__restrict__ items,
+                                                 const int *__restrict__ n_items,
+                                                 const float4 *__restrict__ sorted,
+                                                 const int *__restrict__ offsets,
+                                                 const int *__restrict__ perm,
+                                                 const int *__restrict__ mass_mixed, ForceParams fp,
+                                                 float4 *__restrict__ subsums)
 {
-    __shared__ float4 tile[kTile];
-    __shared__ Stencil st;
+    __shared__ ItemShared sh;
     const int n = *n_items;
     for (int pos = item_position(blockIdx.x); pos < n; pos += gridDim.x)
-        process_item(B, items[pos], sorted, offsets, perm, mass_mixed, fp, tile, st, threadIdx.x,
+        process_item(B, items[pos], sorted, offsets, perm, mass_mixed, fp, sh, threadIdx.x,
                      subsums);
 }
 
 // Adds the partial sums of the sub-items of every chunk cut into sub-items
 // (heads: each chunk's first sub-item), in sub-item order -- sub-item 0's
 // sums are in the outputs already -- and writes the chunk's accelerations
-// (passive targets' partials are exact zeros).
-// Thread g of the grid-stride loop takes target g % kChunk2 of head g / kChunk2.
+// (passive targets' partials are exact zeros).  One wavefront per head
+// (grid-stride), two targets per lane at most.  Latency-bound: the planes of a
+// target are all loaded before the first is added.
 __global__ __launch_bounds__(256) void k_subsum(Batch B, const int4 *__restrict__ heads,
                                                 const int *__restrict__ n_heads,
                                                 const int *__restrict__ perm,
                                                 const float4 *__restrict__ subsums)
 {
-    const long long n = (long long)*n_heads * kChunk2;
-    for (long long g = (long long)blockIdx.x * 256 + threadIdx.x; g < n;
-         g += (long long)gridDim.x * 256) {
-        const int4 item = heads[g / kChunk2];
-        const int t = (int)(g % kChunk2);
+    const int n = *n_heads, lane = threadIdx.x & 63;
+    for (int h = blockIdx.x * 4 + (threadIdx.x >> 6); h < n; h += gridDim.x * 4) {
+        const int4 item = heads[h];
         const int ns = item_nsub(item);
         const BoxDesc &d = box_at(B, item_box(item));
-        if (t < item.z) {
+        for (int t = lane; t < item.z; t += 64) {
             const int slot = item.y + t;
+            float4 v[kMaxSrcSplit - 1];
+#pragma unroll
+            for (int k = 0; k < kMaxSrcSplit - 1; ++k)
+                v[k] = k < ns - 1 ? subsums[(size_t)k * B.ntot + slot]
+                                  : make_float4(0.f, 0.f, 0.f, 0.f);
             const int orig = perm[slot] - d.pbase;
             float ax = d.ax[orig], ay = d.ay[orig], az = d.az[orig];
-            for (int k = 1; k < ns; ++k) {
-                const float4 v = subsums[(size_t)(k - 1) * B.ntot + slot];
-                ax += v.x;
-                ay += v.y;
-                az += v.z;
-            }
+#pragma unroll
+            for (int k = 0; k < kMaxSrcSplit - 1; ++k)
+                if (k < ns - 1) {
+                    ax += v[k].x;
+                    ay += v[k].y;
+                    az += v[k].z;
+                }
             d.ax[orig] = ax;
             d.ay[orig] = ay;
             d.az[orig] = az;
@@ -255,31 +112,31 @@ __global__ __launch_bounds__(256) void k_subsum(Batch B, const int4 *__restrict_
 // workgroup reaches the exit).  Taking two per atomic halves the traffic on
 // the one counter address, which bounded the pass on many-item batches.
 constexpr int kPersistentGrab = 2;
-__global__ __launch_bounds__(64) void k_force_persistent(Batch B, const int4 *__restrict__ items,
-                                                         const int *__restrict__ n_items,
-                                                         const float4 *__restrict__ sorted,
-                                                         const int *__restrict__ offsets,
-                                                         const int *__restrict__ perm,
-                                                         const int *__restrict__ mass_mixed,
-                                                         ForceParams fp, int *__restrict__ queue,
-                                                         float4 *__restrict__ subsums)
+__global__ __launch_bounds__(64, 8) void k_force_persistent(Batch B, const int4 *__restrict__ items,
+                                                            const int *__restrict__ n_items,
+                                                            const float4 *__restrict__ sorted,
+                                                            const int *__restrict__ offsets,
+                                                            const int *__restrict__ perm,
+                                                            const int *__restrict__ mass_mixed,
+                                                            ForceParams fp,
+                                                            int *__restrict__ queue,
+                                                            float4 *__restrict__ subsums)
 {
-    __shared__ float4 tile[kTile];
-    __shared__ Stencil st;
+    __shared__ ItemShared sh;
     __shared__ int next;
     const int n = *n_items;
     for (;;) {
         if (threadIdx.x == 0)
             next = atomicAdd(queue, kPersistentGrab);
         __syncthreads();
-        const int p0 = next;
+        const int p0 = __builtin_amdgcn_readfirstlane(next);
         __syncthreads();
         if (p0 >= n)
             break;
         const int pe = p0 + kPersistentGrab < n ? p0 + kPersistentGrab : n;
         for (int pos = p0; pos < pe; ++pos)
-            process_item(B, items[pos], sorted, offsets, perm, mass_mixed, fp, tile, st,
-                         threadIdx.x, subsums);
+            process_item(B, items[pos], sorted, offsets, perm, mass_mixed, fp, sh, threadIdx.x,
+                         subsums);
     }
 }
 
@@ -366,12 +223,11 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
     }
 }
 
-// Work items of a block of 256 cells: each thread takes one cell's chunk
-// count and stencil size (cells flagged kFineFlag are chunked here: long
-// chunks cut into sub-items, short ones finer; with split, the chunks of
-// boxes that box_splits admits are cut into sub-items by their pair count;
-// with target counts, a masked pass, the chunks cover the cell's first
-// tcount[c] slots, where its active particles sit), the block
+// Work items of a block of kItemCells cells: each of the first kItemCells
+// threads takes one cell's chunk and sub-item counts (with split, the chunks of
+// boxes that box_splits admits, and of any box in masked passes, are cut by
+// cell_cut; with target counts, a masked pass, the chunks cover the cell's
+// first tcount[c] slots, where its active particles sit), the block
 // reserves its item range with one atomic on *n_items, then all threads
 // write the block's items, thread j the items j, j + 256, ... (the cell of an
 // item found by a binary search over the block's running item counts).  The
@@ -379,78 +235,57 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // every target is summed in a fixed order, by one item or by its chunk's
 // sub-items added in order.  The first sub-item of every cut chunk is also
 // appended to heads, for k_subsum.
+constexpr int kItemCells = 64;
 __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ offsets,
-                                               const int *__restrict__ chunk_count,
+                                               const int *__restrict__ cell_src,
+                                               const unsigned long long *__restrict__ work,
                                                const int *__restrict__ tcount, int split,
                                                int4 *__restrict__ items,
                                                int *__restrict__ item_cost,
                                                int *__restrict__ n_items,
                                                int4 *__restrict__ heads,
-                                               int *__restrict__ n_heads)
+                                               int *__restrict__ n_heads,
+                                               int *__restrict__ lpt)
 {
-    __shared__ int wsum[4];
     __shared__ int base;
-    __shared__ int s_end[256];  // the block's items up to and including each cell
-    __shared__ int s_q[256], s_ns[256], s_b[256], s_len[256], s_box[256];
-    __shared__ long long s_src[256];
-    __shared__ bool s_mesh[256];  // chunks laid out as mesh_chunks lays them out, or equal
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    // masked passes: the counts binning left; otherwise the cell's chunks
-    const int cc = c >= B.ctot ? 0
-                   : tcount    ? chunk_count[c]
-                               : mesh_chunks(offsets[c + 1] - offsets[c]);
-    const bool fine = (cc & kFineFlag) != 0;
-    int q = cc & (kFineFlag - 1);
-    int ns = 1, box = 0, b = 0, len = 0;
-    bool mesh = true;
-    long long src = 0;
-    if (q > 0 || fine) {
-        src = cell_stencil(B, offsets, c, &box, &b, &len);
-        if (tcount)
-            len = tcount[c];  // the active particles, sorted to the front of the cell
-        long long k = 1;
-        if (fine) {
-            // long chunks (dense cells): whole chunks cut into sub-items by
-            // their pair count; short ones: chunks of at most kFineChunk
-            // targets cut by their source count, so that passes over few
-            // cells still have many items
-            const int qm = mesh_chunks(len);
-            const long long pm = src * ((len + qm - 1) / qm);
-            const bool whole = pm > kSplitPairs;
-            mesh = whole;
-            q = whole ? qm : (len + kFineChunk - 1) / kFineChunk;
-            k = whole ? (pm + kSplitPairs - 1) / kSplitPairs
-                      : (src + kFineSources - 1) / kFineSources;
-        } else if (split && box_splits(box_at(B, box).n)) {
-            k = (src * ((len + q - 1) / q) + kSplitPairs - 1) / kSplitPairs;
+    __shared__ int hist[32];  // the block's items per cost bucket, for the longest-first order
+    if (threadIdx.x >= 64 && threadIdx.x < 96)
+        hist[threadIdx.x - 64] = 0;
+    __shared__ int s_end[kItemCells];  // the block's items up to and including each cell
+    __shared__ int s_q[kItemCells], s_ns[kItemCells], s_b[kItemCells], s_len[kItemCells];
+    __shared__ int s_box[kItemCells], s_full[kItemCells], s_src[kItemCells];
+    if (threadIdx.x < kItemCells) {
+        static_assert(kItemCells == 64, "one wavefront counts the block's items");
+        const int c = blockIdx.x * kItemCells + threadIdx.x;
+        const int b = c < B.ctot ? offsets[c] : 0;
+        // masked passes: the active particles, sorted to the front of the cell
+        const int len = c >= B.ctot ? 0 : (tcount ? tcount[c] : offsets[c + 1] - b);
+        int q = 0, ns = 1, box = 0, full = kChunk2, src = 0;
+        if (len > 0) {
+            box = find_box(B.cstart, B.nb, c);
+            src = cell_src[c];
+            if (split && (tcount || box_splits(box_at(B, box).n)))
+                ns = cell_cut(len, src, work[box], &full);
+            q = mesh_chunks(len, full);
         }
-        ns = k < 1 ? 1 : (k > kMaxSrcSplit ? kMaxSrcSplit : (int)k);
+        const int m = q * ns;
+        int tot;
+        const int first = wave_exclusive_scan(m, threadIdx.x, &tot);
+        if (threadIdx.x == 0)
+            base = tot > 0 ? atomicAdd(n_items, tot) : 0;
+        s_end[threadIdx.x] = first + m;
+        s_q[threadIdx.x] = q;
+        s_ns[threadIdx.x] = ns;
+        s_b[threadIdx.x] = b;
+        s_len[threadIdx.x] = len;
+        s_box[threadIdx.x] = box;
+        s_src[threadIdx.x] = src;
+        s_full[threadIdx.x] = full;
     }
-    const int m = q * ns;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int tot;
-    int first = wave_exclusive_scan(m, lane, &tot);
-    if (lane == 0)
-        wsum[wid] = tot;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int t = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        base = t > 0 ? atomicAdd(n_items, t) : 0;
-    }
-    for (int j = 0; j < wid; ++j)
-        first += wsum[j];
-    s_end[threadIdx.x] = first + m;
-    s_q[threadIdx.x] = q;
-    s_ns[threadIdx.x] = ns;
-    s_b[threadIdx.x] = b;
-    s_len[threadIdx.x] = len;
-    s_box[threadIdx.x] = box;
-    s_src[threadIdx.x] = src;
-    s_mesh[threadIdx.x] = mesh;
-    __syncthreads();
-    const int T = s_end[255];
+    const int T = s_end[kItemCells - 1];
     for (int j = threadIdx.x; j < T; j += 256) {
-        int lo = 0, hi = 255;
+        int lo = 0, hi = kItemCells - 1;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (s_end[mid] > j)
@@ -462,44 +297,29 @@ __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ 
         const int r = j - (s_end[lo] - qq * nn);
         const int k = r / nn;
         int bucket;
-        const int4 it = cell_item(blockIdx.x * 256 + lo, s_box[lo], s_b[lo], s_len[lo], qq,
-                                  s_mesh[lo], k, nn, r - k * nn, s_src[lo], &bucket);
+        const int4 it = cell_item(blockIdx.x * kItemCells + lo, s_box[lo], s_b[lo], s_len[lo], qq,
+                                  s_full[lo], k, nn, r - k * nn, s_src[lo], &bucket);
         items[base + j] = it;
         item_cost[base + j] = bucket;
+        atomicAdd(&hist[31 - bucket], 1);
         if (nn > 1 && r == k * nn)
             heads[atomicAdd(n_heads, 1)] = it;
     }
+    __syncthreads();
+    if (threadIdx.x < 32 && hist[threadIdx.x] > 0)
+        atomicAdd(&lpt[threadIdx.x], hist[threadIdx.x]);
 }
 
 // Longest-first order of the items: a counting sort by decreasing cost
-// bucket (key = 31 - bucket).  k_lpt_hist adds every block's key counts into
-// 32 global totals; k_lpt_scatter gives key k the range starting at the
-// totals of the keys before it, reserves one sub-range per (block, key) with
-// an atomic, and places its items there in their original order.  Which
+// bucket (key = 31 - bucket).  The kernels that write the items add their key
+// counts into 32 global totals; k_lpt_scatter gives key k the range starting at
+// the totals of the keys before it, reserves one sub-range per (block, key)
+// with an atomic, and places its items there in their original order.  Which
 // block gets which sub-range depends on timing, so the item order inside a
 // key is not fixed -- results are: every target is summed entirely inside
 // one item, in a fixed order, whatever the order of the items.
-// lpt[0..31] are the key totals and lpt[32..63] the key cursors, both zero
-// on entry (the binning pass clears them).
-__global__ __launch_bounds__(256) void k_lpt_hist(const int *__restrict__ item_cost,
-                                                  const int *__restrict__ n_items,
-                                                  int *__restrict__ lpt)
-{
-    __shared__ int h[32];
-    if (threadIdx.x < 32)
-        h[threadIdx.x] = 0;
-    __syncthreads();
-    const int n = *n_items;
-    for (int k = 0; k < kLptBlock / 256; ++k) {
-        const int i = blockIdx.x * kLptBlock + k * 256 + threadIdx.x;
-        if (i < n)
-            atomicAdd(&h[31 - item_cost[i]], 1);
-    }
-    __syncthreads();
-    if (threadIdx.x < 32 && h[threadIdx.x] > 0)
-        atomicAdd(&lpt[threadIdx.x], h[threadIdx.x]);
-}
-
+// lpt[0..31] are the key totals and lpt[32..63] the key cursors, all zero
+// before the items are written (the binning pass clears them).
 __global__ __launch_bounds__(256) void k_lpt_scatter(const int4 *__restrict__ items,
                                                      const int *__restrict__ item_cost,
                                                      const int *__restrict__ n_items,
@@ -619,7 +439,7 @@ __global__ __launch_bounds__(256) void k_momentum_final(const double *__restrict
 }
 
 constexpr unsigned kMaskedGrid = 65536;  // workgroups of a masked pass at most (a multiple of 512)
-constexpr unsigned kSubsumGrid = 256;    // workgroups of k_subsum (256 threads each)
+constexpr unsigned kSubsumGrid = 1024;   // workgroups of k_subsum (256 threads each)
 
 unsigned grid_for_items(int64_t ub)
 {
@@ -637,8 +457,7 @@ int64_t item_bound(int64_t ntot, int64_t ctot, bool split)
 {
     int64_t nonempty = ntot < ctot ? ntot : ctot;
     // at most max(ceil(n / 64), n / 16) <= n / 16 + 1 chunks per cell
-    // (mesh_chunks_for; flagged cells take ceil(n / kFineChunk) <= n / 32 + 1),
-    // each of at most kMaxSrcSplit sub-items when chunks may be cut
+    // (mesh_chunks_for), each of at most kMaxSrcSplit sub-items when chunks may be cut
     const int64_t chunks = nonempty + ntot / 16 + 1;
     return split ? kMaxSrcSplit * chunks : chunks;
 }
@@ -653,7 +472,6 @@ void force_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, ForceScratch &s, 
     s.offsets = b.take<int>((size_t)ctot + 1);
     s.perm = b.take<int>(nn);
     s.sorted = b.take<float4>(nn);
-    s.chunk_count = b.take<int>((size_t)ctot);
     s.items = b.take<int4>((size_t)ub);
     s.item_cost = b.take<int>((size_t)ub);
     s.items_lpt = b.take<int4>((size_t)ub);
@@ -729,9 +547,7 @@ ForceParams make_params(float r_max, float eps, const float *poly)
 int lpt_sort_enqueue(sr_ctx *ctx, const int4 *items, const int *item_cost, const int *n_items,
                      int64_t bound, int *lpt, int4 *out)
 {
-    const int nblk = lpt_blocks(bound);
-    hipLaunchKernelGGL(k_lpt_hist, dim3(nblk), dim3(256), 0, ctx->stream, item_cost, n_items, lpt);
-    hipLaunchKernelGGL(k_lpt_scatter, dim3(nblk), dim3(256), 0, ctx->stream, items, item_cost,
+    hipLaunchKernelGGL(k_lpt_scatter, dim3(lpt_blocks(bound)), dim3(256), 0, ctx->stream, items, item_cost,
                        n_items, lpt, out);
     return sr_check_launch(ctx, "k_lpt");
 }
@@ -741,11 +557,12 @@ int lpt_sort_enqueue(sr_ctx *ctx, const int4 *items, const int *item_cost, const
 static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s, int order)
 {
     int rc;
-    if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, s.chunk_count, s.tcount)))
+    if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, s.tcount, true)))
         return rc;
-    hipLaunchKernelGGL(k_items, dim3((B.ctot + 255) / 256), dim3(256), 0, ctx->stream, B,
-                       s.offsets, s.chunk_count, s.tcount, s.part != nullptr ? 1 : 0, s.items,
-                       s.item_cost, s.bin.n_items, s.heads, s.bin.n_heads);
+    hipLaunchKernelGGL(k_items, dim3((B.ctot + kItemCells - 1) / kItemCells), dim3(256), 0,
+                       ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
+                       s.part != nullptr ? 1 : 0, s.items, s.item_cost, s.bin.n_items, s.heads,
+                       s.bin.n_heads, s.bin.lpt);
     if ((rc = sr_check_launch(ctx, "k_items")))
         return rc;
     if (order == 1)

@@ -89,9 +89,9 @@ struct BoxDesc {
     int pbase, n, cbase, _pad;
     const float *x, *y, *z, *m;   // positions, or cell offsets when g.split
     const int *cell3;             // split coordinates: packed chaining cells
-    // optional, single-box passes: 0 inactive, 1 active, 2 active and its
-    // cell cut into finer items; only active particles are targets (every
-    // particle stays a source) and only their accelerations are written
+    // optional, single-box passes: 0 inactive, 1 active; only active particles
+    // are targets (every particle stays a source) and only their accelerations
+    // are written
     const unsigned char *active;
     float *ax, *ay, *az;
 };
@@ -175,16 +175,18 @@ struct Bump {
 struct BinScratch {
     int *cid;         // [ntot] global cell id of each particle
     int *slot;        // [ntot] arrival rank within its cell (atomic, unordered)
-    int *count;       // [ctot] particles per cell
+    int *count;       // [ctot] particles per cell, then stencil sources per cell (k_gather)
     int *scan_part;   // [scan tiles] partial sums
     int *tmp;         // [ntot] ping-pong buffer of the large-cell merge
     int *large_list;  // cells too big for one wavefront's LDS, by size class
     int *large_count; // [9] large cells per size class, then the block sort's work counter
     int *mass_mixed;  // [nb] box b: 1 if any of its masses differs from its first
-    int *scan_flag;   // [1] last-block counter of the scans (kept at 0)
     int *lpt;         // [64] key totals and cursors of the longest-first item order
-    int *n_items;     // [1] force work items appended by k_items
-    int *n_heads;     // [1] chunks cut into sub-items, appended by k_items
+    int *counters;    // [kCounters] the single counters below, cleared together
+    int *scan_flag;   // last-block counter of the scans (kept at 0)
+    int *n_items;     // force work items appended by k_items
+    int *n_heads;     // chunks cut into sub-items, appended by k_items
+    unsigned long long *work;  // [nb] target-source pairs of boxes that cut their chunks
     // radix-sort binning (passes of many particles; null otherwise)
     int *vtmp;        // [ntot] index ping-pong buffer
     int *ktmp;        // [ntot] key ping-pong buffer (with tmp; cid keeps the ids)
@@ -205,7 +207,6 @@ struct ForceScratch {
     int *offsets;     // [ctot + 1]
     int *perm;        // [ntot]
     float4 *sorted;   // [ntot] (x, y, z, m) in cell order
-    int *chunk_count; // [ctot] masked passes: activity flags, then chunks per cell
     int4 *items;      // [item bound] in cell order
     int *item_cost;   // [item bound] cost bucket of each item
     int4 *items_lpt;  // [item bound] items by decreasing cost bucket
@@ -222,6 +223,7 @@ constexpr int kChunk = 64;         // maximum targets per work item at one targe
 constexpr int kChunk2 = 128;       // ... and at two targets per lane (chaining-mesh pass)
 constexpr int kMaxSplit = 16;      // at most 16 lane groups share one target
 constexpr int kLptBlock = 1024;    // items per block of the cost-bucket sort
+constexpr int kCounters = 3;
 
 // Looks up the device address of sr_force_static's fixed scratch array on
 // `device` (current) once (sr_noalloc.hip).
@@ -239,19 +241,17 @@ void sr_timing_mark(sr_ctx *ctx, int rec, int which);
 // Binning (sr_bin.hip)
 void bin_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, BinScratch &s);
 int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, int *perm,
-                float4 *sorted, int *chunk_count, int *tcount);
+                float4 *sorted, int *tcount, bool items);
 void scan_layout(Bump &b, int m, int **part);
 int scan_enqueue(sr_ctx *ctx, const int *in, int m, int *part, int *out, int *flag);
 int fill_enqueue(sr_ctx *ctx, int *p, int value, int64_t count);
 int clear_enqueue(sr_ctx *ctx, const ClearList &cl);
 
 // Force pass (sr_force.hip)
-// Items of a pass at most; masked: a pass with an activity mask, whose
-// flagged cells may take finer items and sub-items.
+// Items of a pass at most; split: chunks may be cut into sub-items.
 int64_t item_bound(int64_t ntot, int64_t ctot, bool split = false);
-// masked: a pass with an activity mask (its flagged cells are cut into
-// sub-items); split_ok: some box of the pass may cut its chunks
-// (box_splits).  Either gives the pass sub-item storage.
+// masked: a pass with an activity mask; split_ok: some box of the pass may
+// cut its chunks (box_splits).  Either gives the pass sub-item storage.
 void force_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, ForceScratch &s, bool masked,
                   bool split_ok);
 int check_box_args(sr_ctx *ctx, const sr_box *box, double cell, float r_max, int xsplit,
@@ -259,7 +259,8 @@ int check_box_args(sr_ctx *ctx, const sr_box *box, double cell, float r_max, int
 int check_force_params(sr_ctx *ctx, float r_max, float eps, const float *poly);
 ForceParams make_params(float r_max, float eps, const float *poly);
 // Longest-first order (counting sort on 5-bit cost buckets) of the *n_items
-// items; bound >= the item count; lpt: int[64], zero on entry (BinScratch).
+// items; bound >= the item count; lpt: int[64], the items per 31 - bucket, then
+// 32 zeros (BinScratch).
 int lpt_sort_enqueue(sr_ctx *ctx, const int4 *items, const int *item_cost, const int *n_items,
                      int64_t bound, int *lpt, int4 *out);
 int single_batch(sr_ctx *ctx, const float *x, const float *y, const float *z, const float *mass,
@@ -398,73 +399,85 @@ __device__ __forceinline__ int tree_chunks(int n)
     return n <= 4 * kChunk ? (n > 0 ? kChunkTab.tree[n] : 0) : (n + kChunk - 1) / kChunk;
 }
 
-// Beyond 4 kChunk targets: full chunks of kChunk2, then the remaining
-// kChunk2 + 1 .. 2 kChunk2 targets cut as the small-cell table cuts them.
-// Against ceil(n / kChunk2) equal chunks this leaves fewer lanes idle: a
-// full chunk fills all 64 lanes at two targets per lane, and only the
-// remainder's chunks may not (a CPU model of the item shapes puts the idle
-// share of the pair loop's issue slots on nfw256 at 0.6 % against 2.6 %).
-__device__ __forceinline__ int mesh_full_chunks(int n)
+// Beyond 4 kChunk targets: full chunks of `full` targets (cell_cut), then the
+// remaining full + 1 .. 2 full targets cut as the small-cell table cuts them.
+// Against equal chunks this leaves fewer lanes idle: a full chunk fills all 64
+// lanes, and only the remainder's chunks may not (a CPU model of the item
+// shapes puts the idle share of the pair loop's issue slots on nfw256 at 0.6 %
+// against 2.6 %).
+__device__ __forceinline__ int mesh_full_chunks(int n, int full)
 {
-    return n > 4 * kChunk ? (n - kChunk2 - 1) / kChunk2 : 0;
+    return n > 4 * kChunk ? (n - full - 1) / full : 0;
 }
 
-__device__ __forceinline__ int mesh_chunks(int n)
+__device__ __forceinline__ int mesh_chunks(int n, int full)
 {
     if (n <= 4 * kChunk)
         return n > 0 ? kChunkTab.mesh[n] : 0;
-    const int full = mesh_full_chunks(n);
-    return full + kChunkTab.mesh[n - full * kChunk2];
+    const int q = mesh_full_chunks(n, full);
+    return q + kChunkTab.mesh[n - q * full];
 }
 
-// Targets [*lo, *hi) of chunk k of q of a cell of len targets: with mesh,
-// the layout of mesh_chunks (q its count), else q nearly equal parts [k len /
-// q, (k + 1) len / q).
-__device__ __forceinline__ void chunk_range(int len, int q, int k, bool mesh, int *lo, int *hi)
+// Targets [*lo, *hi) of chunk k of the q = mesh_chunks(len, full) chunks of a
+// cell of len targets.
+__device__ __forceinline__ void chunk_range(int len, int q, int k, int full, int *lo, int *hi)
 {
-    int base = 0;
-    if (mesh && len > 4 * kChunk) {
-        const int full = mesh_full_chunks(len);
-        if (k < full) {
-            *lo = k * kChunk2;
-            *hi = *lo + kChunk2;
-            return;
-        }
-        base = full * kChunk2;
-        len -= base;
-        q -= full;
-        k -= full;
+    const int nf = mesh_full_chunks(len, full);
+    if (k < nf) {
+        *lo = k * full;
+        *hi = *lo + full;
+        return;
     }
-    // k len fits in 32 bits below 46341 targets (q <= len)
-    const bool small = len <= 46340;
-    *lo = base + (small ? k * len / q : (int)((long long)k * len / q));
-    *hi = base + (small ? (k + 1) * len / q : (int)((long long)(k + 1) * len / q));
+    // the remainder, at most 4 kChunk targets, in nearly equal parts
+    const int base = nf * full;
+    len -= base;
+    q -= nf;
+    k -= nf;
+    *lo = base + k * len / q;
+    *hi = base + (k + 1) * len / q;
 }
 
 // Work items.  A cell's targets are cut into q chunks (chunk_range); a chunk
-// is one item, or ns sub-items that take
-// consecutive parts [sk T / ns, (sk + 1) T / ns) of the T stencil sources,
-// so that the pairs of a dense cell spread over more wavefronts and no
-// single wavefront holds up the end of the pass (a chunk of P target-source
-// pairs takes ceil(P / kSplitPairs) sub-items, at most kMaxSrcSplit).  Cells
-// flagged for finer items (multilevel passes) are cut so in any box, and
-// their short chunks into chunks of at most kFineChunk targets instead.  A
-// sub-item leaves partial sums, which a second pass adds in sub-item order.
-constexpr int kMaxSrcSplit = 8;       // sub-items per chunk at most
-constexpr int kFineChunk = 32;        // targets per item of short chunks in flagged cells
-constexpr int kFineSources = 4096;    // stencil sources per sub-item of those chunks, about
-constexpr long long kSplitPairs = 1 << 20;  // target-source pairs per sub-item, about
-constexpr int64_t kSplitMaxN = 1 << 22;     // boxes of at most this many particles cut other chunks
+// is one item, or ns sub-items that take consecutive parts [sk T / ns,
+// (sk + 1) T / ns) of the T stencil sources, so that the pairs of a dense cell
+// spread over more wavefronts and no single wavefront holds up the end of the
+// pass.  A sub-item leaves partial sums, which a second pass adds in sub-item
+// order.
+constexpr int kMaxSrcSplit = 8;          // sub-items per chunk at most
+constexpr int64_t kSplitMaxN = 1 << 22;  // plain passes: boxes of at most this many particles cut
 
-// Whether the chunks of a box of n particles (other than those of cells
-// flagged for finer items) may be cut into sub-items: a property of the box
-// alone, so that a box gives the same sums alone and in a batch.  Larger
-// boxes have enough items to keep every wavefront busy to the end.
+// Whether the chunks of a box of n particles may be cut into sub-items in
+// passes without an activity mask: a property of the box alone, so that a box
+// gives the same sums alone and in a batch.  Larger boxes have enough items to
+// keep every wavefront busy to the end.
 __host__ __device__ inline bool box_splits(int64_t n)
 {
     return n <= kSplitMaxN;
 }
-constexpr int kFineFlag = 1 << 30;    // chunk_count bit: cell flagged for finer items
+
+// How a cell of len targets with src stencil sources each is cut in a box of
+// `work` target-source pairs that cuts its chunks: items of about work / 32768
+// pairs, i.e. four for each of the 8192 wavefronts that run at once, so that
+// the longest item stays a small part of the pass; at least kItemPairs, below
+// which an item's own work (stencil, box, output: some 2000 instructions)
+// outweighs its pairs, and at most 2^18.  A property of the box alone.  Chunks
+// of kChunk2 targets are halved, twice at most, where kMaxSrcSplit sub-items
+// are not enough.  Returns the sub-items per chunk.
+constexpr long long kItemPairs = 1 << 16;
+
+__device__ __forceinline__ int cell_cut(int len, int src, unsigned long long work, int *full)
+{
+    long long t = (long long)(work >> 14);
+    t = t < kItemPairs ? kItemPairs : (t > (1 << 18) ? (1 << 18) : t);
+    int f = kChunk2;
+    while (f > kChunk2 / 4 && (long long)src * (len < f ? len : f) > kMaxSrcSplit * t)
+        f >>= 1;
+    *full = f;
+    const long long q = mesh_chunks(len, f);
+    const long long k = (src * ((len + q - 1) / q) + t - 1) / t;
+    return k < 1 ? 1 : (k > kMaxSrcSplit ? kMaxSrcSplit : (int)k);
+}
+
 constexpr int kMaxBatchBoxes = 1 << 17;
 
 // Item layout: {cell (global), first sorted slot, targets, S | (tpl - 1) << 5
@@ -474,21 +487,17 @@ __host__ __device__ inline int item_word(int S, int tpl, int sk, int ns, int box
     return S | (tpl - 1) << 5 | sk << 6 | (ns - 1) << 10 | box << 14;
 }
 
-// Stencil size of cell c (global id): the sources of its 9 x-rows of 2 hx + 1
-// cells (shifts aside); also its box, first sorted slot and particle count.
-__device__ inline long long cell_stencil(const Batch &B, const int *__restrict__ offsets, int c,
-                                         int *box_out, int *b_out, int *len_out)
+// Stencil size of cell c (global id) of box d: the sources of its 9 x-rows of
+// 2 hx + 1 cells (shifts aside).
+__device__ inline int cell_stencil(const BoxDesc &d, const int *__restrict__ offsets, int c)
 {
-    const int box = find_box(B.cstart, B.nb, c);
-    const BoxDesc &d = box_at(B, box);
     const Geom &g = d.g;
-    const int b = offsets[c];
-    const int len = offsets[c + 1] - b;
     const int lc = c - d.cbase, plane = g.nc[0] * g.nc[1];
-    const int cz = lc / plane, cy = (lc - cz * plane) / g.nc[0];
+    const int cz = div_by(lc, g.div_m[0], g.div_s[0]);
+    const int cy = div_by(lc - cz * plane, g.div_m[1], g.div_s[1]);
     const int cx = lc - cz * plane - cy * g.nc[0];
     const int *off = offsets + d.cbase;
-    long long src = 0;
+    int src = 0;
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
         int ny = cy + r % 3 - 1, nz = cz + r / 3 - 1;
@@ -512,22 +521,19 @@ __device__ inline long long cell_stencil(const Batch &B, const int *__restrict__
             src += off[row + e + 1] - off[row + a];
         }
     }
-    *box_out = box;
-    *b_out = b;
-    *len_out = len;
     return src;
 }
 
 // Sub-item sk of chunk k of a cell (first sorted slot b, len targets, q
-// chunks laid out as mesh_chunks lays them out (mesh) or equal, ns sub-items
-// per chunk, src stencil sources), shaped by item_shape;
+// chunks of `full` targets, ns sub-items per chunk, src stencil sources),
+// shaped by item_shape;
 // *bucket is floor(log2(cost)), cost = (the sub-item's sources) x (the
 // shape's cost per source) + 64 (wavefront iterations plus overhead).
-__device__ inline int4 cell_item(int c, int box, int b, int len, int q, bool mesh, int k, int ns,
-                                 int sk, long long src, int *bucket)
+__device__ inline int4 cell_item(int c, int box, int b, int len, int q, int full, int k, int ns,
+                                 int sk, int src, int *bucket)
 {
     int lo, hi;
-    chunk_range(len, q, k, mesh, &lo, &hi);
+    chunk_range(len, q, k, full, &lo, &hi);
     int tpl, S;
     const float pass = item_shape(hi - lo, &tpl, &S);
     const long long cost = (long long)((float)(src / ns) * pass) + 64;

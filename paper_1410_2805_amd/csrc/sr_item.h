@@ -1,0 +1,302 @@
+// The pair loop of a chaining-mesh work item (sr_force.hip): one wavefront, at
+// most 64 vector registers and 5 KiB of LDS, so that 8 wavefronts share a SIMD.
+//
+// The stencil's sources pass by in windows of 64, one per lane: each is tested
+// against the box of the item's targets (source_kept), and the kept ones are
+// appended to a tile in LDS.  When the tile cannot take another window, the S
+// lane groups take equal slices of the whole quanta (4 S sources) it holds,
+// and what is left moves to its front.  So no source is padding but at the
+// item's end, and only one window waits in registers (5 of them) instead of a
+// tile of 256 (16).
+//
+// What bounds it: FP32 VALU issue.  FMA, multiply, add and subtract issue two
+// at a time from different wavefronts (2.2 cycles each per SIMD), compare,
+// select, min and max do not (4.1), v_rsq_f32 takes 8.  The more wavefronts
+// share a SIMD the more often two are ready: a register-only probe of the loop
+// on all 256 CUs reaches 2.41e12 pairs/s at 5 wavefronts per SIMD, 2.83e12 at
+// 8, and 2.88e12 at 8 with the cutoff as EXEC mask (pair_masked).
+#pragma once
+
+#include "sr_pair.h"
+
+namespace {
+
+constexpr int kWindow = 64;          // sources tested at a time
+constexpr int kStage = 2 * kWindow;  // tile: what a pass leaves (< kWindow) and one window
+constexpr int kSumTile = 256;        // sources in a partial sum at most
+
+// acc: each lane's sums so far, added to once per partial sum, so that they
+// hold no registers through the pair loop.
+struct ItemShared {
+    float4 tile[kStage + 2];  // pair_slice reads two entries past a slice
+    Stencil st;
+    float acc[6][64];
+};
+
+// One or two targets of a lane and their partial sums.
+struct LaneTargets {
+    float xi, yi, zi, xj, yj, zj;
+    float tx, ty, tz, ux, uy, uz;
+};
+
+// pair_one (sr_pair.h) with the cutoff as EXEC mask on the accumulation: the
+// same products and sums for a pair within the cutoff, and nothing added for
+// one beyond it, where pair_one adds 0.  One v_cmpx takes the place of v_cmp
+// and v_cndmask.  All 64 lanes are active before and after (64-thread
+// workgroups, wave-uniform control flow): EXEC is restored to all ones.  n4 is
+// fp.nq[4] in a vector register (an instruction reads one scalar one).
+template <bool kUniformMass>
+__device__ __forceinline__ void pair_masked(const float4 &s, float xi, float yi, float zi,
+                                            const ForceParams &fp, const ForceParams &w, float &tx, float &ty,
+                                            float &tz)
+{
+    const float dx = s.x - xi;
+    const float dy = s.y - yi;
+    const float dz = s.z - zi;
+    const float se = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, w.eps)));
+    const float rs = __builtin_amdgcn_rsqf(se);
+    const float rs2 = rs * rs;
+    const float tt = fmaf(rs2, rs, -w.q0);
+    float h = fmaf(w.nq[5], se, w.nq[4]);
+    h = fmaf(h, se, w.nq[3]);
+    h = fmaf(h, se, w.nq[2]);
+    h = fmaf(h, se, w.nq[1]);
+    float f = fmaf(h, se, tt);
+    if (!kUniformMass)
+        f *= s.w;
+    asm("v_cmpx_gt_f32 vcc, %6, %7\n\t"
+        "v_fmac_f32 %0, %3, %4\n\t"
+        "v_fmac_f32 %1, %3, %5\n\t"
+        "v_fmac_f32 %2, %3, %8\n\t"
+        "s_mov_b64 exec, -1"
+        : "+v"(tx), "+v"(ty), "+v"(tz)
+        : "v"(f), "v"(dx), "v"(dy), "s"(fp.rcut), "v"(se), "v"(dz)
+        : "vcc");
+}
+
+// A lane's targets with sources src[0 .. cnt), cnt a positive multiple of 4,
+// each target summed in source order: two sources at a time, the next two on
+// their way from LDS while two are evaluated.  The barriers keep the compiler
+// from interleaving more than four pairs, which takes more than 64 registers.
+template <bool kTwo, bool kUniformMass>
+__device__ __forceinline__ void pair_slice(const float4 *src, int cnt, const ForceParams &fp,
+                                           LaneTargets &L)
+{
+    ForceParams w = fp;
+    asm volatile("" : "+v"(w.eps), "+v"(w.q0), "+v"(w.nq[1]), "+v"(w.nq[2]), "+v"(w.nq[3]), "+v"(w.nq[4]), "+v"(w.nq[5]));
+    auto both = [&](const float4 &a, const float4 &b) {
+        pair_masked<kUniformMass>(a, L.xi, L.yi, L.zi, fp, w, L.tx, L.ty, L.tz);
+        if (kTwo)
+            pair_masked<kUniformMass>(a, L.xj, L.yj, L.zj, fp, w, L.ux, L.uy, L.uz);
+        pair_masked<kUniformMass>(b, L.xi, L.yi, L.zi, fp, w, L.tx, L.ty, L.tz);
+        if (kTwo)
+            pair_masked<kUniformMass>(b, L.xj, L.yj, L.zj, fp, w, L.ux, L.uy, L.uz);
+    };
+    do {
+        const float4 a0 = src[0], a1 = src[1];
+        both(a0, a1);
+        src += 2;
+        cnt -= 2;
+    } while (cnt > 0);
+}
+
+// Adds a lane's partial sums to its sums in LDS and clears them.
+__device__ __forceinline__ void flush_sums(ItemShared &sh, int lane, LaneTargets &L)
+{
+    sh.acc[0][lane] += L.tx;
+    sh.acc[1][lane] += L.ty;
+    sh.acc[2][lane] += L.tz;
+    sh.acc[3][lane] += L.ux;
+    sh.acc[4][lane] += L.uy;
+    sh.acc[5][lane] += L.uz;
+    L.tx = L.ty = L.tz = L.ux = L.uy = L.uz = 0.f;
+}
+
+// Source gi = g + lane of the stencil, without its shift; far, massless padding
+// from `end` on.  p is the piece of the lane's last source and moves on to
+// this one's.
+__device__ __forceinline__ float4 load_window(const Stencil &st, const float4 *__restrict__ sorted,
+                                              int g, int end, int lane, int &p)
+{
+    float4 v = make_float4(kFar, kFar, kFar, 0.f);
+    const int gi = g + lane;
+    if (gi < end) {
+        while (gi >= st.pbeg[p + 1])
+            ++p;
+        v = sorted[st.psrc[p] + (gi - st.pbeg[p])];
+    }
+    return v;
+}
+
+// Sources [g0, g1) of the item's stencil.  part: the lane's group, below S.
+template <bool kTwo, bool kUniformMass>
+__device__ __forceinline__ void item_sources(int S, int part, int g0, int g1,
+                                             const float4 *__restrict__ sorted,
+                                             const ForceParams &fp, int lane, ItemShared &sh,
+                                             LaneTargets &L)
+{
+    const TargetBox tb = target_box(L.xi, L.yi, L.zi, L.xj, L.yj, L.zj);
+    const int quantum = 4 * S, qrecip = kItemTab.qrecip[S];
+    int fill = 0, summed = 0, p = 0;
+    float4 v = load_window(sh.st, sorted, g0, g1, lane, p);
+    for (int g = g0; g < g1; g += kWindow) {
+        const Shift3 s = sh.st.psh[p];
+        v.x += s.x;
+        v.y += s.y;
+        v.z += s.z;
+        const bool kept = source_kept(v, tb, fp);
+        const unsigned long long mask = __ballot(kept);
+        if (kept)
+            sh.tile[fill + (int)__builtin_amdgcn_mbcnt_hi(
+                               (unsigned)(mask >> 32),
+                               __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u))] = v;
+        fill += __popcll(mask);
+        const bool last = g + kWindow >= g1;
+        if (!last) {
+            v = load_window(sh.st, sorted, g + kWindow, g1, lane, p);
+            if (fill <= kStage - kWindow)
+                continue;
+        }
+        // whole quanta: at the end the last one is filled up with far, massless
+        // sources (fill < kStage: as many as a quantum fit)
+        int n = (fill * qrecip) >> 16;
+        if (last && n * quantum < fill) {
+            ++n;
+            if (fill + lane < n * quantum)
+                sh.tile[fill + lane] = make_float4(kFar, kFar, kFar, 0.f);
+        }
+        if (n == 0)
+            continue;
+        __syncthreads();
+        pair_slice<kTwo, kUniformMass>(sh.tile + part * (4 * n), 4 * n, fp, L);
+        const int done = n * quantum;
+        fill -= done;
+        summed += done;
+        if (fill > 0) {
+            const float4 r = sh.tile[done + (lane < fill ? lane : 0)];
+            __syncthreads();
+            if (lane < fill)
+                sh.tile[lane] = r;
+        }
+        if (last || summed > kSumTile - kStage) {
+            summed = 0;
+            flush_sums(sh, lane, L);
+        }
+    }
+    flush_sums(sh, lane, L);
+}
+
+// The targets of lane `lane` of an item of nt targets: group part of S, t and
+// the second one t2 when it holds two (lane t of a group holds targets t and
+// t + ln, ln lanes per group).  Lanes past the groups repeat the first ones.
+struct ItemLane {
+    int ln, part, t, t2;
+    bool has, has2;
+};
+
+__device__ __forceinline__ ItemLane item_lane(bool two, int nt, int S, int lane)
+{
+    ItemLane T;
+    T.ln = two ? (nt + 1) >> 1 : nt;
+    T.part = lane_group(lane, T.ln);
+    T.t = lane - T.part * T.ln;
+    T.has = T.part < S;
+    T.part = T.has ? T.part : 0;
+    T.has2 = two && T.has && T.t + T.ln < nt;
+    T.t2 = T.has2 ? T.t + T.ln : T.t;
+    return T;
+}
+
+// Stores the acceleration of the target in a sorted slot: sub-item 0 writes it
+// as a whole item does, sub-item sub > 0 its partial sums to plane sub - 1.
+__device__ __forceinline__ void write_target(const BoxDesc &d, const int *__restrict__ perm,
+                                             float4 *__restrict__ subsums, int ntot, int sub,
+                                             int slot, bool passive, float ax, float ay, float az)
+{
+    if (passive)
+        ax = ay = az = 0.f;
+    if (sub > 0) {
+        subsums[(size_t)(sub - 1) * ntot + slot] = make_float4(ax, ay, az, 0.f);
+    } else {
+        const int orig = perm[slot] - d.pbase;
+        d.ax[orig] = ax;
+        d.ay[orig] = ay;
+        d.az[orig] = az;
+    }
+}
+
+// The pair loop of one work item by one wavefront.
+__device__ __forceinline__ void process_item(const Batch &B, const int4 item,
+                                             const float4 *__restrict__ sorted,
+                                             const int *__restrict__ offsets,
+                                             const int *__restrict__ perm,
+                                             const int *__restrict__ mass_mixed,
+                                             const ForceParams &fp, ItemShared &sh, int lane,
+                                             float4 *__restrict__ subsums)
+{
+    const int kb = item.y, nt = item.z, S = item_split(item), box = item_box(item);
+    const BoxDesc &d = box_at(B, box);
+    const Geom &g = d.g;
+    const bool two = item_two(item), uniform = mass_mixed[box] == 0;
+    ItemLane T = item_lane(two, nt, S, lane);
+    float4 pt = sorted[kb + T.t], pt2 = sorted[kb + T.t2];
+    const bool work = __any((T.has && !is_passive(pt, g)) || (T.has2 && !is_passive(pt2, g)));
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        sh.acc[k][lane] = 0.f;
+    if (work) {
+        int cx, cy, cz;
+        decode_cell(item.x - d.cbase, g, cx, cy, cz);
+        const int cc[3] = {cx, cy, cz};
+        float F[3];
+        frame_shift(g, cc, F);
+        build_stencil(sh.st, offsets + d.cbase, g, cx, cy, cz, F, lane);
+        __syncthreads();
+        // a sub-item takes its part [sk T / ns, (sk + 1) T / ns) of the T sources
+        const int ns = item_nsub(item), sk = item_sub(item);
+        const int all = __builtin_amdgcn_readfirstlane(sh.st.pbeg[kMaxPieces]);
+        int g0 = 0, g1 = all;
+        if (ns > 1) {
+            g0 = __builtin_amdgcn_readfirstlane((int)((long long)sk * all / ns));
+            g1 = __builtin_amdgcn_readfirstlane((int)((long long)(sk + 1) * all / ns));
+        }
+        LaneTargets L = {pt.x + F[0], pt.y + F[1], pt.z + F[2], pt2.x + F[0], pt2.y + F[1],
+                         pt2.z + F[2], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (two) {
+            if (uniform)
+                item_sources<true, true>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+            else
+                item_sources<true, false>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+        } else {
+            if (uniform)
+                item_sources<false, true>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+            else
+                item_sources<false, false>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+        }
+        // found and read again instead of held through the pair loop
+        asm volatile("" : "+v"(lane));
+        T = item_lane(two, nt, S, lane);
+        pt = sorted[kb + T.t];
+        pt2 = sorted[kb + T.t2];
+        __syncthreads();
+    }
+    // the S group sums of each target in group order, by the first group
+    if (lane < T.ln) {
+        float a[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            a[k] = sh.acc[k][lane];
+            for (int q = 1; q < S; ++q)
+                a[k] += sh.acc[k][lane + q * T.ln];
+        }
+        const float m = uniform ? pt.w : 1.f, m2 = uniform ? pt2.w : 1.f;
+        write_target(d, perm, subsums, B.ntot, item_sub(item), kb + T.t, is_passive(pt, g),
+                     a[0] * m, a[1] * m, a[2] * m);
+        if (T.has2)
+            write_target(d, perm, subsums, B.ntot, item_sub(item), kb + T.t2, is_passive(pt2, g),
+                         a[3] * m2, a[4] * m2, a[5] * m2);
+    }
+    __syncthreads();  // the next item replaces the pieces and the sums
+}
+
+}  // namespace

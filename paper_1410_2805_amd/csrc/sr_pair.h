@@ -14,10 +14,13 @@ constexpr float kFar = 1.0e6f;   // padding source far outside any box, mass 0
 // wraps) in global coordinates, at most 63 (one per cell) in split
 // coordinates.  pbeg[npiece] = all sources; unused pieces are empty.
 constexpr int kMaxPieces = 64;
+struct Shift3 {
+    float x, y, z;
+};
 struct Stencil {
     int pbeg[kMaxPieces + 1];  // prefix of piece lengths
     int psrc[kMaxPieces];      // first sorted slot of each piece
-    float4 psh[kMaxPieces];    // shift added to the piece's coordinates
+    Shift3 psh[kMaxPieces];    // shift added to the piece's coordinates
 };
 
 __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int *total)
@@ -33,17 +36,19 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int *total)
     return inc - v;
 }
 
-// Builds the source pieces of target cell (cx, cy, cz) into st (all lanes
-// call).  Global coordinates: lanes < 18 each own one piece slot, row r =
-// lane/2, half = lane%2, the shift is the periodic image shift.  Split
-// coordinates: lanes < 9 (2 hx + 1) each own one cell of the stencil and the
-// shift is the cell's offset from the target cell, (dx w0, dy w1, dz w2), so
-// coordinates stay cell-relative and periodic wrap needs no shift at all.
-__device__ void build_stencil(Stencil &st, const int *__restrict__ offsets, const Geom &g, int cx,
-                              int cy, int cz, const float F[3], int lane)
+// Source piece `lane` of target cell (cx, cy, cz): first sorted slot, length
+// (0: no such piece) and the shift added to its coordinates.  Global
+// coordinates: lanes < 18 each own one piece slot, row r = lane/2, half =
+// lane%2, the shift is the periodic image shift.  Split coordinates: lanes <
+// 9 (2 hx + 1) each own one cell of the stencil and the shift is the cell's
+// offset from the target cell, (dx w0, dy w1, dz w2), so coordinates stay
+// cell-relative and periodic wrap needs no shift at all.
+__device__ __forceinline__ void stencil_piece(const int *__restrict__ offsets, const Geom &g, int cx,
+                                              int cy, int cz, const float F[3], int lane, int &src,
+                                              int &len, float &sx, float &sy, float &sz)
 {
-    int len = 0, src = 0;
-    float sx = 0.f, sy = 0.f, sz = 0.f;
+    len = src = 0;
+    sx = sy = sz = 0.f;
     const int W = 2 * g.hx + 1;
     if (g.split && lane < 9 * W) {
         const int r = lane / W, k = lane - r * W;
@@ -102,11 +107,20 @@ __device__ void build_stencil(Stencil &st, const int *__restrict__ offsets, cons
         sy = shy;
         sz = shz;
     }
-    int total;
+}
+
+// Builds the source pieces of target cell (cx, cy, cz) into st (all lanes
+// call).
+__device__ void build_stencil(Stencil &st, const int *__restrict__ offsets, const Geom &g, int cx,
+                              int cy, int cz, const float F[3], int lane)
+{
+    int len, src, total;
+    float sx, sy, sz;
+    stencil_piece(offsets, g, cx, cy, cz, F, lane, src, len, sx, sy, sz);
     int beg = wave_exclusive_scan(len, lane, &total);
     st.pbeg[lane] = beg;
     st.psrc[lane] = src;
-    st.psh[lane] = make_float4(sx, sy, sz, 0.f);
+    st.psh[lane] = Shift3{sx, sy, sz};
     if (lane == 0)
         st.pbeg[kMaxPieces] = total;
 }
@@ -159,7 +173,7 @@ __device__ __forceinline__ void load_tile(float4 (&pre)[kTile / 64], const Stenc
             while (gi >= st.pbeg[p + 1])
                 ++p;
             const float4 s = sorted[st.psrc[p] + (gi - st.pbeg[p])];
-            const float4 sh = st.psh[p];
+            const Shift3 sh = st.psh[p];
             v = make_float4(s.x + sh.x, s.y + sh.y, s.z + sh.z, s.w);
         }
         pre[k] = v;

@@ -256,17 +256,14 @@ __device__ __forceinline__ bool ml_kicks(int l, int m, int M)
     return t % M == 0 && ((t / M) & 1);
 }
 
-// Particles that kick after piece m: 1, or 2 above the lowest level.  The
-// short-range pass cuts the cells holding a 2 into finer work items: such a
-// pass runs over few, dense cells, and one wavefront per large chunk would
-// leave most of the GPU idle.
+// Particles that kick after piece m.
 __global__ __launch_bounds__(kBlock) void k_ml_active(const unsigned char *__restrict__ level,
-                                                      int n, int m, int M, int lmin,
+                                                      int n, int m, int M,
                                                       unsigned char *__restrict__ active)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n)
-        active[i] = ml_kicks(level[i], m, M) ? (level[i] > lmin ? 2 : 1) : 0;
+        active[i] = ml_kicks(level[i], m, M) ? 1 : 0;
 }
 
 // After stream piece m: particles of a level that kicks at m take v += a tau/l
@@ -486,13 +483,13 @@ int ml_levels_enqueue(sr_ctx *ctx, const SplitGeom &sg, const int *cell3, int n,
     return sr_check_launch(ctx, "k_ml_level");
 }
 
-int ml_active_enqueue(sr_ctx *ctx, const unsigned char *level, int n, int m, int M, int lmin,
+int ml_active_enqueue(sr_ctx *ctx, const unsigned char *level, int n, int m, int M,
                       unsigned char *active)
 {
     if (n <= 0)
         return SR_OK;
     hipLaunchKernelGGL(k_ml_active, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, ctx->stream,
-                       level, n, m, M, lmin, active);
+                       level, n, m, M, active);
     return sr_check_launch(ctx, "k_ml_active");
 }
 

@@ -53,7 +53,7 @@ extern "C" int sr_ksk_step(sr_ctx *ctx, sr_pm *pm, int32_t *cell3, float *ox, fl
     unsigned char *level = nullptr, *active = nullptr;
     int *counts = nullptr;
     if (ml) {
-        // sized for a masked pass (finer items, sub-item sums); the sizing
+        // sized for a masked pass (sub-item sums); the sizing
         // call only tests the mask pointer for null
         static const unsigned char any_mask = 1;
         size_t fbytes = 0;
@@ -119,7 +119,7 @@ extern "C" int sr_ksk_step(sr_ctx *ctx, sr_pm *pm, int32_t *cell3, float *ox, fl
                 if (!kicks_at(m))
                     continue;  // its stream piece went with the last kick's launch
                 const int ns = streams_after(m);
-                if ((rc = ml_active_enqueue(ctx, level, ni, m, M, p->ml_min, active)) ||
+                if ((rc = ml_active_enqueue(ctx, level, ni, m, M, active)) ||
                     (rc = force_split_masked(ctx, cell3, ox, oy, oz, mass, n, box, p->cell,
                                              p->r_max, p->eps, p->poly, sr_ax, sr_ay, sr_az,
                                              nullptr, active, nullptr)) ||

@@ -396,8 +396,13 @@ __global__ __launch_bounds__(256) void k_leaf_items(Batch B, int n, const int *_
                                                     const int *__restrict__ offsets,
                                                     const int *__restrict__ item_off,
                                                     int4 *__restrict__ items,
-                                                    int *__restrict__ item_cost)
+                                                    int *__restrict__ item_cost,
+                                                    int *__restrict__ lpt)
 {
+    __shared__ int hist[32];  // the block's items per cost bucket, for the longest-first order
+    if (threadIdx.x < 32)
+        hist[threadIdx.x] = 0;
+    __syncthreads();
     const int nleaves = lscan[n];
     const Geom &g = B.one.g;
     for (int l = blockIdx.x * 256 + threadIdx.x; l < nleaves; l += gridDim.x * 256) {
@@ -427,9 +432,14 @@ __global__ __launch_bounds__(256) void k_leaf_items(Batch B, int n, const int *_
             const float pass = item_shape(hi - lo, &tpl, &S);
             items[item_off[l] + k] = make_int4(l, a + lo, hi - lo, S | (tpl - 1) << 5);
             const long long cost = (long long)((float)src * pass) + 64;
-            item_cost[item_off[l] + k] = 63 - __clzll((unsigned long long)cost);
+            const int bucket = 63 - __clzll((unsigned long long)cost);
+            item_cost[item_off[l] + k] = bucket;
+            atomicAdd(&hist[31 - bucket], 1);
         }
     }
+    __syncthreads();
+    if (threadIdx.x < 32 && hist[threadIdx.x] > 0)
+        atomicAdd(&lpt[threadIdx.x], hist[threadIdx.x]);
 }
 
 // Leaf of every original particle: the inclusive count of leaf starts - 1.
@@ -481,7 +491,7 @@ __device__ __forceinline__ void shift_tile(float4 (&pre)[kTile / 64], unsigned p
 {
 #pragma unroll
     for (int k = 0; k < kTile / 64; ++k) {
-        const float4 sh = st.psh[(pk >> (8 * k)) & 255u];
+        const Shift3 sh = st.psh[(pk >> (8 * k)) & 255u];
         pre[k].x += sh.x;
         pre[k].y += sh.y;
         pre[k].z += sh.z;
@@ -652,7 +662,7 @@ __device__ void process_leaf_item(const Batch &B, const int4 item,
                 const int slot = npiece + __popcll(bal & ((1ull << lane) - 1ull));
                 st.psrc[slot] = src;
                 st.pbeg[slot] = total + ex;
-                st.psh[slot] = make_float4(sh[0], sh[1], sh[2], 0.f);
+                st.psh[slot] = Shift3{sh[0], sh[1], sh[2]};
             }
             npiece += k;
             total += tot;
@@ -729,7 +739,7 @@ int tree_prep(sr_ctx *ctx, const Batch &B, const ForceScratch &s, const TreeScra
 {
     int rc;
     const int n = B.ntot;
-    if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, nullptr, nullptr)))
+    if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, nullptr, false)))
         return rc;
     if ((rc = fill_enqueue(ctx, t.flag, 0, n > 0 ? n : 1)) || (rc = fill_enqueue(ctx, t.flag0, 0, 1)))
         return rc;
@@ -759,7 +769,7 @@ int tree_items(sr_ctx *ctx, const Batch &B, const ForceScratch &s, const TreeScr
         return rc;
     hipLaunchKernelGGL(k_leaf_items, dim3(blocks_of(n, 256) < 4096 ? blocks_of(n, 256) : 4096),
                        dim3(256), 0, ctx->stream, B, n, t.lscan, t.leaf_start, t.leaf_cell,
-                       s.offsets, t.item_off, t.items, t.item_cost);
+                       s.offsets, t.item_off, t.items, t.item_cost, s.bin.lpt);
     if ((rc = sr_check_launch(ctx, "k_leaf_items")))
         return rc;
     return lpt_sort_enqueue(ctx, t.items, t.item_cost, t.item_off + n, tree_item_bound(n),
