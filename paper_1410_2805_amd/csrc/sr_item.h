@@ -4,10 +4,12 @@
 // The stencil's sources pass by in windows of 64, one per lane: each is tested
 // against the box of the item's targets (source_kept), and the kept ones are
 // appended to a tile in LDS.  When the tile cannot take another window, the S
-// lane groups take equal slices of the whole quanta (4 S sources) it holds,
-// and what is left moves to its front.  So no source is padding but at the
-// item's end, and only one window waits in registers (5 of them) instead of a
-// tile of 256 (16).
+// lane groups take the whole quanta (2 S sources) it holds in turn, group q
+// the sources q, q + S, q + 2 S, ... (consecutive entries at a time, so that the
+// groups' reads meet no common LDS bank: with contiguous slices two in five
+// LDS cycles of the 128^3 lattice pass were conflicts), and what is left moves
+// to its front.  So no source is padding but at the item's end, and only one
+// window waits in registers (5 of them) instead of a tile of 256 (16).
 //
 // What bounds it: FP32 VALU issue.  FMA, multiply, add and subtract issue two
 // at a time from different wavefronts (2.2 cycles each per SIMD), compare,
@@ -25,11 +27,24 @@ constexpr int kWindow = 64;          // sources tested at a time
 constexpr int kStage = 2 * kWindow;  // tile: what a pass leaves (< kWindow) and one window
 constexpr int kSumTile = 256;        // sources in a partial sum at most
 
+// The non-empty source pieces of an item's cell: piece k holds the stencil's
+// sources [beg[k], beg[k + 1]), source g of it sits in sorted slot g +
+// rec[k].off, and its shift is added to its coordinates.  beg past the pieces is
+// the number of all sources.
+struct PieceRec {
+    int off;
+    float x, y, z;
+};
+struct Pieces {
+    PieceRec rec[kMaxPieces];
+    int beg[kMaxPieces + 2];
+};
+
 // acc: each lane's sums so far, added to once per partial sum, so that they
 // hold no registers through the pair loop.
 struct ItemShared {
-    float4 tile[kStage + 2];  // pair_slice reads two entries past a slice
-    Stencil st;
+    float4 tile[kStage];
+    Pieces st;
     float acc[6][64];
 };
 
@@ -43,11 +58,10 @@ struct LaneTargets {
 // same products and sums for a pair within the cutoff, and nothing added for
 // one beyond it, where pair_one adds 0.  One v_cmpx takes the place of v_cmp
 // and v_cndmask.  All 64 lanes are active before and after (64-thread
-// workgroups, wave-uniform control flow): EXEC is restored to all ones.  n4 is
-// fp.nq[4] in a vector register (an instruction reads one scalar one).
+// workgroups, wave-uniform control flow): EXEC is restored to all ones.
 template <bool kUniformMass>
 __device__ __forceinline__ void pair_masked(const float4 &s, float xi, float yi, float zi,
-                                            const ForceParams &fp, const ForceParams &w, float &tx, float &ty,
+                                            const ForceParams &w, float rcut, float &tx, float &ty,
                                             float &tz)
 {
     const float dx = s.x - xi;
@@ -70,34 +84,30 @@ __device__ __forceinline__ void pair_masked(const float4 &s, float xi, float yi,
         "v_fmac_f32 %2, %3, %8\n\t"
         "s_mov_b64 exec, -1"
         : "+v"(tx), "+v"(ty), "+v"(tz)
-        : "v"(f), "v"(dx), "v"(dy), "s"(fp.rcut), "v"(se), "v"(dz)
+        : "v"(f), "v"(dx), "v"(dy), "s"(rcut), "v"(se), "v"(dz)
         : "vcc");
 }
 
-// A lane's targets with sources src[0 .. cnt), cnt a positive multiple of 4,
-// each target summed in source order: two sources at a time, the next two on
-// their way from LDS while two are evaluated.  The barriers keep the compiler
-// from interleaving more than four pairs, which takes more than 64 registers.
+// A lane's targets with 2 n sources, src[0], src[S], src[2 S], ...  (n > 0),
+// each target summed in source order.  The polynomial's constants sit in vector
+// registers: of two instructions issued together one may read a scalar one.
 template <bool kTwo, bool kUniformMass>
-__device__ __forceinline__ void pair_slice(const float4 *src, int cnt, const ForceParams &fp,
-                                           LaneTargets &L)
+__device__ __forceinline__ void pair_run(const float4 *src, int S, int n, const ForceParams &fp,
+                                         LaneTargets &L)
 {
     ForceParams w = fp;
-    asm volatile("" : "+v"(w.eps), "+v"(w.q0), "+v"(w.nq[1]), "+v"(w.nq[2]), "+v"(w.nq[3]), "+v"(w.nq[4]), "+v"(w.nq[5]));
-    auto both = [&](const float4 &a, const float4 &b) {
-        pair_masked<kUniformMass>(a, L.xi, L.yi, L.zi, fp, w, L.tx, L.ty, L.tz);
-        if (kTwo)
-            pair_masked<kUniformMass>(a, L.xj, L.yj, L.zj, fp, w, L.ux, L.uy, L.uz);
-        pair_masked<kUniformMass>(b, L.xi, L.yi, L.zi, fp, w, L.tx, L.ty, L.tz);
-        if (kTwo)
-            pair_masked<kUniformMass>(b, L.xj, L.yj, L.zj, fp, w, L.ux, L.uy, L.uz);
-    };
+    asm volatile("" : "+v"(w.eps), "+v"(w.q0), "+v"(w.nq[1]), "+v"(w.nq[2]), "+v"(w.nq[3]),
+                      "+v"(w.nq[4]), "+v"(w.nq[5]));
     do {
-        const float4 a0 = src[0], a1 = src[1];
-        both(a0, a1);
-        src += 2;
-        cnt -= 2;
-    } while (cnt > 0);
+        const float4 a = src[0], b = src[S];
+        src += 2 * S;
+        pair_masked<kUniformMass>(a, L.xi, L.yi, L.zi, w, fp.rcut, L.tx, L.ty, L.tz);
+        if (kTwo)
+            pair_masked<kUniformMass>(a, L.xj, L.yj, L.zj, w, fp.rcut, L.ux, L.uy, L.uz);
+        pair_masked<kUniformMass>(b, L.xi, L.yi, L.zi, w, fp.rcut, L.tx, L.ty, L.tz);
+        if (kTwo)
+            pair_masked<kUniformMass>(b, L.xj, L.yj, L.zj, w, fp.rcut, L.ux, L.uy, L.uz);
+    } while (--n > 0);
 }
 
 // Adds a lane's partial sums to its sums in LDS and clears them.
@@ -112,38 +122,67 @@ __device__ __forceinline__ void flush_sums(ItemShared &sh, int lane, LaneTargets
     L.tx = L.ty = L.tz = L.ux = L.uy = L.uz = 0.f;
 }
 
+// Builds the pieces of target cell (cx, cy, cz) (all lanes call); returns whether
+// any is shifted.
+__device__ __forceinline__ bool build_pieces(Pieces &st, const int *__restrict__ offsets,
+                                             const Geom &g, int cx, int cy, int cz,
+                                             const float F[3], int lane)
+{
+    int len, src, total;
+    float sx, sy, sz;
+    stencil_piece(offsets, g, cx, cy, cz, F, lane, src, len, sx, sy, sz);
+    const int beg = wave_exclusive_scan(len, lane, &total);
+    const unsigned long long some = __ballot(len > 0);
+    const int k = (int)__builtin_amdgcn_mbcnt_hi(
+        (unsigned)(some >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)some, 0u));
+    if (len > 0) {
+        st.rec[k] = PieceRec{src - beg, sx, sy, sz};
+        st.beg[k] = beg;
+    }
+    const int np = __popcll(some);
+    for (int e = np + lane; e < kMaxPieces + 2; e += 64)
+        st.beg[e] = total;
+    return __any(len > 0 && (sx != 0.f || sy != 0.f || sz != 0.f));
+}
+
 // Source gi = g + lane of the stencil, without its shift; far, massless padding
 // from `end` on.  p is the piece of the lane's last source and moves on to
-// this one's.
-__device__ __forceinline__ float4 load_window(const Stencil &st, const float4 *__restrict__ sorted,
+// this one's: two pieces at a time, further where pieces are short.
+__device__ __forceinline__ float4 load_window(const Pieces &st, const float4 *__restrict__ sorted,
                                               int g, int end, int lane, int &p)
 {
     float4 v = make_float4(kFar, kFar, kFar, 0.f);
     const int gi = g + lane;
     if (gi < end) {
-        while (gi >= st.pbeg[p + 1])
-            ++p;
-        v = sorted[st.psrc[p] + (gi - st.pbeg[p])];
+        for (;;) {
+            const int b1 = st.beg[p + 1], b2 = st.beg[p + 2];
+            p += (gi >= b1 ? 1 : 0) + (gi >= b2 ? 1 : 0);
+            if (gi < b2)
+                break;
+        }
+        v = sorted[gi + st.rec[p].off];
     }
     return v;
 }
 
 // Sources [g0, g1) of the item's stencil.  part: the lane's group, below S.
 template <bool kTwo, bool kUniformMass>
-__device__ __forceinline__ void item_sources(int S, int part, int g0, int g1,
+__device__ __forceinline__ void item_sources(int S, int part, int g0, int g1, bool shifted,
                                              const float4 *__restrict__ sorted,
                                              const ForceParams &fp, int lane, ItemShared &sh,
                                              LaneTargets &L)
 {
     const TargetBox tb = target_box(L.xi, L.yi, L.zi, L.xj, L.yj, L.zj);
-    const int quantum = 4 * S, qrecip = kItemTab.qrecip[S];
+    const int quantum = 2 * S, qrecip = kItemTab.srecip[S];
     int fill = 0, summed = 0, p = 0;
     float4 v = load_window(sh.st, sorted, g0, g1, lane, p);
     for (int g = g0; g < g1; g += kWindow) {
-        const Shift3 s = sh.st.psh[p];
-        v.x += s.x;
-        v.y += s.y;
-        v.z += s.z;
+        if (shifted) {
+            const PieceRec r = sh.st.rec[p];
+            v.x += r.x;
+            v.y += r.y;
+            v.z += r.z;
+        }
         const bool kept = source_kept(v, tb, fp);
         const unsigned long long mask = __ballot(kept);
         if (kept)
@@ -168,17 +207,18 @@ __device__ __forceinline__ void item_sources(int S, int part, int g0, int g1,
         if (n == 0)
             continue;
         __syncthreads();
-        pair_slice<kTwo, kUniformMass>(sh.tile + part * (4 * n), 4 * n, fp, L);
+        pair_run<kTwo, kUniformMass>(sh.tile + part, S, n, fp, L);
         const int done = n * quantum;
         fill -= done;
-        summed += done;
+        summed += 2 * n;
         if (fill > 0) {
             const float4 r = sh.tile[done + (lane < fill ? lane : 0)];
             __syncthreads();
             if (lane < fill)
                 sh.tile[lane] = r;
         }
-        if (last || summed > kSumTile - kStage) {
+        // partial sums of at most kSumTile sources
+        if (summed > kSumTile - kStage) {
             summed = 0;
             flush_sums(sh, lane, L);
         }
@@ -250,11 +290,12 @@ __device__ __forceinline__ void process_item(const Batch &B, const int4 item,
         const int cc[3] = {cx, cy, cz};
         float F[3];
         frame_shift(g, cc, F);
-        build_stencil(sh.st, offsets + d.cbase, g, cx, cy, cz, F, lane);
+        const bool shifted =
+            build_pieces(sh.st, offsets + d.cbase, g, cx, cy, cz, F, lane);
         __syncthreads();
         // a sub-item takes its part [sk T / ns, (sk + 1) T / ns) of the T sources
         const int ns = item_nsub(item), sk = item_sub(item);
-        const int all = __builtin_amdgcn_readfirstlane(sh.st.pbeg[kMaxPieces]);
+        const int all = __builtin_amdgcn_readfirstlane(sh.st.beg[kMaxPieces]);
         int g0 = 0, g1 = all;
         if (ns > 1) {
             g0 = __builtin_amdgcn_readfirstlane((int)((long long)sk * all / ns));
@@ -264,14 +305,17 @@ __device__ __forceinline__ void process_item(const Batch &B, const int4 item,
                          pt2.z + F[2], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (two) {
             if (uniform)
-                item_sources<true, true>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+                item_sources<true, true>(S, T.part, g0, g1, shifted, sorted, fp, lane, sh, L);
             else
-                item_sources<true, false>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+                item_sources<true, false>(S, T.part, g0, g1, shifted, sorted, fp, lane, sh,
+                                          L);
         } else {
             if (uniform)
-                item_sources<false, true>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+                item_sources<false, true>(S, T.part, g0, g1, shifted, sorted, fp, lane, sh,
+                                          L);
             else
-                item_sources<false, false>(S, T.part, g0, g1, sorted, fp, lane, sh, L);
+                item_sources<false, false>(S, T.part, g0, g1, shifted, sorted, fp, lane, sh,
+                                           L);
         }
         // found and read again instead of held through the pair loop
         asm volatile("" : "+v"(lane));
@@ -284,11 +328,12 @@ __device__ __forceinline__ void process_item(const Batch &B, const int4 item,
     if (lane < T.ln) {
         float a[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
+        for (int k = 0; k < 6; ++k)
             a[k] = sh.acc[k][lane];
-            for (int q = 1; q < S; ++q)
+        for (int q = 1; q < S; ++q)
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
                 a[k] += sh.acc[k][lane + q * T.ln];
-        }
         const float m = uniform ? pt.w : 1.f, m2 = uniform ? pt2.w : 1.f;
         write_target(d, perm, subsums, B.ntot, item_sub(item), kb + T.t, is_passive(pt, g),
                      a[0] * m, a[1] * m, a[2] * m);

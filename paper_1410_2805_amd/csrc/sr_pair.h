@@ -197,32 +197,29 @@ __device__ __forceinline__ int ordered_key(int b)
     return b ^ ((b >> 31) & 0x7fffffff);
 }
 
-// One step of a row reduction: v combined with lane (ctrl) of its row.
-template <int kCtrl, bool kMax>
-__device__ __forceinline__ int row_step(int v)
+// One step of a wavefront reduction: v combined with the lane that the DPP
+// control names; rows outside kRows keep v.
+template <int kCtrl, int kRows, bool kMax>
+__device__ __forceinline__ int dpp_step(int v)
 {
-    const int o = __builtin_amdgcn_mov_dpp(v, kCtrl, 0xF, 0xF, true);
+    const int o = __builtin_amdgcn_update_dpp(v, v, kCtrl, kRows, 0xF, false);
     return kMax ? max(v, o) : min(v, o);
 }
 
-// Minimum (kMax false) or maximum of a and b over the 64 lanes, uniform: on
-// ordered keys, within each row of 16 lanes by exchanges across pairs,
-// quads, half rows and the row (DPP quad_perm [1,0,3,2], [2,3,0,1], row half
-// mirror, row mirror), then across the four rows' first lanes.
-template <bool kMax>
-__device__ __forceinline__ float wave_extreme(float a, float b)
+// Minima of v[0..2] and maxima of v[3..5] over the 64 lanes, in lane 63: within
+// each row of 16 lanes by exchanges across pairs, quads, half rows and the row
+// (DPP quad_perm [1,0,3,2], [2,3,0,1], row half mirror, row mirror), then the
+// last lane of rows 0 and 2 to rows 1 and 3, and of row 1 to rows 2 and 3.  Step
+// by step for all six: a DPP read waits two instructions for its operand.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void box_step(int (&v)[6])
 {
-    const int ka = ordered_key(__float_as_int(a)), kb = ordered_key(__float_as_int(b));
-    int v = kMax ? max(ka, kb) : min(ka, kb);
-    v = row_step<0xB1, kMax>(v);
-    v = row_step<0x4E, kMax>(v);
-    v = row_step<0x141, kMax>(v);
-    v = row_step<0x140, kMax>(v);
-    const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-    const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    const int m = kMax ? max(max(r0, r1), max(r2, r3)) : min(min(r0, r1), min(r2, r3));
-    // held in a scalar register through the whole item
-    return __int_as_float(ordered_key(__builtin_amdgcn_readfirstlane(m)));
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        v[k] = dpp_step<kCtrl, kRows, false>(v[k]);
+#pragma unroll
+    for (int k = 3; k < 6; ++k)
+        v[k] = dpp_step<kCtrl, kRows, true>(v[k]);
 }
 
 // Every lane passes the two targets it holds (equal when it holds one); the
@@ -230,13 +227,27 @@ __device__ __forceinline__ float wave_extreme(float a, float b)
 __device__ __forceinline__ TargetBox target_box(float xi, float yi, float zi, float xj, float yj,
                                                 float zj)
 {
+    const float p[3] = {xi, yi, zi}, q[3] = {xj, yj, zj};
+    int v[6];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int a = ordered_key(__float_as_int(p[k])), c = ordered_key(__float_as_int(q[k]));
+        v[k] = min(a, c);
+        v[3 + k] = max(a, c);
+    }
+    box_step<0xB1, 0xF>(v);
+    box_step<0x4E, 0xF>(v);
+    box_step<0x141, 0xF>(v);
+    box_step<0x140, 0xF>(v);
+    box_step<0x142, 0xA>(v);
+    box_step<0x143, 0xC>(v);
     TargetBox b;
-    b.lo[0] = wave_extreme<false>(xi, xj);
-    b.lo[1] = wave_extreme<false>(yi, yj);
-    b.lo[2] = wave_extreme<false>(zi, zj);
-    b.hi[0] = wave_extreme<true>(xi, xj);
-    b.hi[1] = wave_extreme<true>(yi, yj);
-    b.hi[2] = wave_extreme<true>(zi, zj);
+    // held in scalar registers through the whole item
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        b.lo[k] = __int_as_float(ordered_key(__builtin_amdgcn_readlane(v[k], 63)));
+        b.hi[k] = __int_as_float(ordered_key(__builtin_amdgcn_readlane(v[3 + k], 63)));
+    }
     return b;
 }
 
@@ -256,12 +267,15 @@ __device__ __forceinline__ bool source_kept(const float4 &s, const TargetBox &b,
 
 // Per lane-group count S (1..16) of an item: the tile capacity cap[S] (a
 // multiple of the slice quantum 4 S) and the quantum's 16-bit fixed-point
-// reciprocal qrecip[S], rounded up, for quanta_of; per target count ln
+// reciprocal qrecip[S], rounded up, for quanta_of; srecip[S] = ceil(2^16 /
+// (2 S)), with which n srecip / 2^16 rounds n / (2 S) down for n < 2048 (it
+// exceeds the quotient by less than n / 2^16 < 1 / 32); per target count ln
 // (1..64) of a group, lnrecip[ln] = ceil(2^16 / ln), for lane_group.  Read
 // with a uniform index, so from scalar memory instead of dividing.
 struct ItemTables {
     int cap[kMaxSplit + 1];
     int qrecip[kMaxSplit + 1];
+    int srecip[kMaxSplit + 1];
     int lnrecip[65];
 };
 
@@ -272,6 +286,7 @@ constexpr ItemTables make_item_tables()
         const int q = 4 * s;
         t.cap[s] = kTile / q * q;
         t.qrecip[s] = (65536 + q - 1) / q;
+        t.srecip[s] = (65536 + 2 * s - 1) / (2 * s);
     }
     for (int l = 1; l <= 64; ++l)
         t.lnrecip[l] = (65536 + l - 1) / l;
