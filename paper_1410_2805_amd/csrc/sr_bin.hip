@@ -1158,6 +1158,7 @@ void bin_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, BinScratch &s)
     s.scan_flag = s.counters;
     s.n_items = s.counters ? s.counters + 1 : nullptr;
     s.n_heads = s.counters ? s.counters + 2 : nullptr;
+    s.n_segs = s.counters ? s.counters + 3 : nullptr;
     s.vtmp = s.ktmp = s.hist = s.hist_part = nullptr;
     if (ntot >= kRadixMinN) {
         const int64_t m = (int64_t)kRadixBins * ((ntot + kRadixTile - 1) / kRadixTile);

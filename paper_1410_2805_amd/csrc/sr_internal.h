@@ -177,7 +177,7 @@ struct BinScratch {
     int *slot;        // [ntot] arrival rank within its cell (atomic, unordered)
     int *count;       // [ctot] particles per cell, then stencil sources per cell (k_gather)
     int *scan_part;   // [scan tiles] partial sums
-    int *tmp;         // [ntot] ping-pong buffer of the large-cell merge
+    int *tmp;         // [ntot] ping-pong buffer of the large-cell merge, then k_items' segments
     int *large_list;  // cells too big for one wavefront's LDS, by size class
     int *large_count; // [9] large cells per size class, then the block sort's work counter
     int *mass_mixed;  // [nb] box b: 1 if any of its masses differs from its first
@@ -186,6 +186,7 @@ struct BinScratch {
     int *scan_flag;   // last-block counter of the scans (kept at 0)
     int *n_items;     // force work items appended by k_items
     int *n_heads;     // chunks cut into sub-items, appended by k_items
+    int *n_segs;      // slot segments to be sub-ordered, appended by k_items (their list: tmp)
     unsigned long long *work;  // [nb] target-source pairs of boxes that cut their chunks
     // radix-sort binning (passes of many particles; null otherwise)
     int *vtmp;        // [ntot] index ping-pong buffer
@@ -223,7 +224,7 @@ constexpr int kChunk = 64;         // maximum targets per work item at one targe
 constexpr int kChunk2 = 128;       // ... and at two targets per lane (chaining-mesh pass)
 constexpr int kMaxSplit = 16;      // at most 16 lane groups share one target
 constexpr int kLptBlock = 1024;    // items per block of the cost-bucket sort
-constexpr int kCounters = 3;
+constexpr int kCounters = 4;
 
 // Looks up the device address of sr_force_static's fixed scratch array on
 // `device` (current) once (sr_noalloc.hip).
