@@ -14,13 +14,10 @@ constexpr float kFar = 1.0e6f;   // padding source far outside any box, mass 0
 // wraps) in global coordinates, at most 63 (one per cell) in split
 // coordinates.  pbeg[npiece] = all sources; unused pieces are empty.
 constexpr int kMaxPieces = 64;
-struct Shift3 {
-    float x, y, z;
-};
 struct Stencil {
     int pbeg[kMaxPieces + 1];  // prefix of piece lengths
     int psrc[kMaxPieces];      // first sorted slot of each piece
-    Shift3 psh[kMaxPieces];    // shift added to the piece's coordinates
+    float4 psh[kMaxPieces];    // shift added to the piece's coordinates
 };
 
 __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int *total)
@@ -120,7 +117,7 @@ __device__ void build_stencil(Stencil &st, const int *__restrict__ offsets, cons
     int beg = wave_exclusive_scan(len, lane, &total);
     st.pbeg[lane] = beg;
     st.psrc[lane] = src;
-    st.psh[lane] = Shift3{sx, sy, sz};
+    st.psh[lane] = make_float4(sx, sy, sz, 0.f);
     if (lane == 0)
         st.pbeg[kMaxPieces] = total;
 }
@@ -173,7 +170,7 @@ __device__ __forceinline__ void load_tile(float4 (&pre)[kTile / 64], const Stenc
             while (gi >= st.pbeg[p + 1])
                 ++p;
             const float4 s = sorted[st.psrc[p] + (gi - st.pbeg[p])];
-            const Shift3 sh = st.psh[p];
+            const float4 sh = st.psh[p];
             v = make_float4(s.x + sh.x, s.y + sh.y, s.z + sh.z, s.w);
         }
         pre[k] = v;

@@ -491,7 +491,7 @@ __device__ __forceinline__ void shift_tile(float4 (&pre)[kTile / 64], unsigned p
 {
 #pragma unroll
     for (int k = 0; k < kTile / 64; ++k) {
-        const Shift3 sh = st.psh[(pk >> (8 * k)) & 255u];
+        const float4 sh = st.psh[(pk >> (8 * k)) & 255u];
         pre[k].x += sh.x;
         pre[k].y += sh.y;
         pre[k].z += sh.z;
@@ -662,7 +662,7 @@ __device__ void process_leaf_item(const Batch &B, const int4 item,
                 const int slot = npiece + __popcll(bal & ((1ull << lane) - 1ull));
                 st.psrc[slot] = src;
                 st.pbeg[slot] = total + ex;
-                st.psh[slot] = Shift3{sh[0], sh[1], sh[2]};
+                st.psh[slot] = make_float4(sh[0], sh[1], sh[2], 0.f);
             }
             npiece += k;
             total += tot;
