@@ -237,10 +237,16 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // appended to heads, for k_subsum.  The target slots of cells of more than
 // kChunk2 targets are appended to segs, in segments of at most kSegLen, for
 // sub_order.
-constexpr int kItemCells = 64;
+//
+// The atomics on the counters bound it where there are many blocks, the longest
+// block where there are few: passes of kManyCells cells or more take 256 cells
+// per block (128^3 lattice, 79507 cells: the pass 585 us with 64, 574 with 256),
+// others 64 (a halo box of 154003 particles 468 against 475 us).
+constexpr int kManyCells = 32768;
 constexpr int kSegThreads = 512;  // threads that order a segment
 constexpr int kSegRounds = 8;     // slots per thread
 constexpr int kSegLen = kSegThreads * kSegRounds;
+template <int kItemCells>
 __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ offsets,
                                                const int *__restrict__ cell_src,
                                                const unsigned long long *__restrict__ work,
@@ -253,20 +259,22 @@ __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ 
                                                int *__restrict__ lpt, int2 *__restrict__ segs,
                                                int *__restrict__ n_segs)
 {
-    __shared__ int base;
+    constexpr int kItemWaves = kItemCells / 64;
+    __shared__ int base, sbase;
+    __shared__ int s_wave[kItemWaves], s_wseg[kItemWaves];  // items and segments per wavefront
     __shared__ int hist[32];  // the block's items per cost bucket, for the longest-first order
-    if (threadIdx.x >= 64 && threadIdx.x < 96)
-        hist[threadIdx.x - 64] = 0;
+    if (threadIdx.x < 32)
+        hist[threadIdx.x] = 0;
     __shared__ int s_end[kItemCells];  // the block's items up to and including each cell
     __shared__ int s_q[kItemCells], s_ns[kItemCells], s_b[kItemCells], s_len[kItemCells];
     __shared__ int s_box[kItemCells], s_full[kItemCells], s_src[kItemCells];
-    if (threadIdx.x < kItemCells) {
-        static_assert(kItemCells == 64, "one wavefront counts the block's items");
-        const int c = blockIdx.x * kItemCells + threadIdx.x;
-        const int b = c < B.ctot ? offsets[c] : 0;
+    const int t = threadIdx.x, w = t >> 6;
+    int q = 0, ns = 1, box = 0, full = kChunk2, src = 0, b = 0, len = 0, first = 0, seg = 0;
+    if (t < kItemCells) {
+        const int c = blockIdx.x * kItemCells + t;
+        b = c < B.ctot ? offsets[c] : 0;
         // masked passes: the active particles, sorted to the front of the cell
-        const int len = c >= B.ctot ? 0 : (tcount ? tcount[c] : offsets[c + 1] - b);
-        int q = 0, ns = 1, box = 0, full = kChunk2, src = 0;
+        len = c >= B.ctot ? 0 : (tcount ? tcount[c] : offsets[c + 1] - b);
         if (len > 0) {
             box = find_box(B.cstart, B.nb, c);
             src = cell_src[c];
@@ -274,33 +282,46 @@ __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ 
                 ns = cell_cut(len, src, work[box], &full);
             q = mesh_chunks(len, full);
         }
-        const int m = q * ns;
-        int tot;
-        const int first = wave_exclusive_scan(m, threadIdx.x, &tot);
-        if (threadIdx.x == 0)
-            base = tot > 0 ? atomicAdd(n_items, tot) : 0;
-        const int ns4 = len > kChunk2 ? (len + kSegLen - 1) / kSegLen : 0;
-        if (__any(ns4 > 0)) {
-            int all, at = wave_exclusive_scan(ns4, threadIdx.x, &all);
-            int sbase = 0;
-            if (threadIdx.x == 0)
-                sbase = atomicAdd(n_segs, all);
-            at += __shfl(sbase, 0, 64);
-            for (int k = 0; k < ns4; ++k)
-                segs[at + k] = make_int2(b + k * kSegLen, len - k * kSegLen < kSegLen
-                                                              ? len - k * kSegLen
-                                                              : kSegLen);
+        const int nseg = len > kChunk2 ? (len + kSegLen - 1) / kSegLen : 0;
+        int tot, all = 0;
+        first = wave_exclusive_scan(q * ns, t & 63, &tot);
+        if (__any(nseg > 0))
+            seg = wave_exclusive_scan(nseg, t & 63, &all);
+        if ((t & 63) == 0) {
+            s_wave[w] = tot;
+            s_wseg[w] = all;
         }
-        s_end[threadIdx.x] = first + m;
-        s_q[threadIdx.x] = q;
-        s_ns[threadIdx.x] = ns;
-        s_b[threadIdx.x] = b;
-        s_len[threadIdx.x] = len;
-        s_box[threadIdx.x] = box;
-        s_src[threadIdx.x] = src;
-        s_full[threadIdx.x] = full;
     }
     __syncthreads();
+    if (t == 0) {
+        int tot = 0, all = 0;
+        for (int v = 0; v < kItemWaves; ++v) {
+            tot += s_wave[v];
+            all += s_wseg[v];
+        }
+        base = tot > 0 ? atomicAdd(n_items, tot) : 0;
+        sbase = all > 0 ? atomicAdd(n_segs, all) : 0;
+    }
+    if (t < kItemCells) {
+        for (int v = 0; v < w; ++v) {
+            first += s_wave[v];
+            seg += s_wseg[v];
+        }
+        s_end[t] = first + q * ns;
+        s_q[t] = q;
+        s_ns[t] = ns;
+        s_b[t] = b;
+        s_len[t] = len;
+        s_box[t] = box;
+        s_src[t] = src;
+        s_full[t] = full;
+    }
+    __syncthreads();
+    if (t < kItemCells && len > kChunk2)
+        for (int k = 0; k * kSegLen < len; ++k)
+            segs[sbase + seg + k] =
+                make_int2(b + k * kSegLen, len - k * kSegLen < kSegLen ? len - k * kSegLen
+                                                                       : kSegLen);
     const int T = s_end[kItemCells - 1];
     for (int j = threadIdx.x; j < T; j += 256) {
         int lo = 0, hi = kItemCells - 1;
@@ -761,8 +782,10 @@ static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s,
     int rc;
     if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, s.tcount, true)))
         return rc;
-    hipLaunchKernelGGL(k_items, dim3((B.ctot + kItemCells - 1) / kItemCells), dim3(256), 0,
-                       ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
+    const bool many = B.ctot >= kManyCells;
+    const int cells = many ? 256 : 64;
+    hipLaunchKernelGGL(many ? k_items<256> : k_items<64>, dim3((B.ctot + cells - 1) / cells),
+                       dim3(256), 0, ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
                        s.part != nullptr ? 1 : 0, s.items, s.item_cost, s.bin.n_items, s.heads,
                        s.bin.n_heads, s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp),
                        s.bin.n_segs);
