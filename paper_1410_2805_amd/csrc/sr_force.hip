@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // cell_cut; with target counts, a masked pass, the chunks cover the cell's
 // first tcount[c] slots, where its active particles sit), the block
 // reserves its item range with one atomic on *n_items, then all threads
-// write the block's items, thread j the items j, j + 256, ... (the cell of an
+// write the block's items, thread j the items j, j + kT, ... (the cell of an
 // item found by a binary search over the block's running item counts).  The
 // order of the items depends on which block reserves first; no result does:
 // every target is summed in a fixed order, by one item or by its chunk's
@@ -241,13 +241,15 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // The atomics on the counters bound it where there are many blocks, the longest
 // block where there are few: passes of kManyCells cells or more take 256 cells
 // per block (128^3 lattice, 79507 cells: the pass 585 us with 64, 574 with 256),
-// others 64 (a halo box of 154003 particles 468 against 475 us).
+// others 64 (a halo box of 154003 particles 468 against 475 us), by 1024 threads:
+// the cells of a halo's core, with thousands of sub-items, sit in one block (that
+// box 460 us with 1024, 469 with 256; an 80^3 halo box 1955 and 1988).
 constexpr int kManyCells = 32768;
 constexpr int kSegThreads = 512;  // threads that order a segment
 constexpr int kSegRounds = 8;     // slots per thread
 constexpr int kSegLen = kSegThreads * kSegRounds;
-template <int kItemCells>
-__global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ offsets,
+template <int kItemCells, int kT>
+__global__ __launch_bounds__(kT) void k_items(Batch B, const int *__restrict__ offsets,
                                                const int *__restrict__ cell_src,
                                                const unsigned long long *__restrict__ work,
                                                const int *__restrict__ tcount, int split,
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) void k_items(Batch B, const int *__restrict__ 
                 make_int2(b + k * kSegLen, len - k * kSegLen < kSegLen ? len - k * kSegLen
                                                                        : kSegLen);
     const int T = s_end[kItemCells - 1];
-    for (int j = threadIdx.x; j < T; j += 256) {
+    for (int j = threadIdx.x; j < T; j += kT) {
         int lo = 0, hi = kItemCells - 1;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
@@ -784,8 +786,8 @@ static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s,
         return rc;
     const bool many = B.ctot >= kManyCells;
     const int cells = many ? 256 : 64;
-    hipLaunchKernelGGL(many ? k_items<256> : k_items<64>, dim3((B.ctot + cells - 1) / cells),
-                       dim3(256), 0, ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
+    const auto kern = many ? k_items<256, 256> : k_items<64, 1024>;
+    hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(many ? 256 : 1024), 0, ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
                        s.part != nullptr ? 1 : 0, s.items, s.item_cost, s.bin.n_items, s.heads,
                        s.bin.n_heads, s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp),
                        s.bin.n_segs);
