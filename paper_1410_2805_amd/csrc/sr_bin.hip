@@ -87,9 +87,12 @@ __global__ void k_fill(int *__restrict__ p, int value, int64_t count)
 
 // Particles per thread of the histogram pass: one up to kCellidSmall particles
 // (a block of 1024 then serializes four rounds on one CU while others idle:
-// 32,768 particles 13.6 us at four per thread), else four (fewer global atomics).
+// 32,768 particles 13.6 us at four per thread), else four: clustered input then
+// adds fewer atomics to the same cells (a halo box of 154003 particles 27 -> 18 us,
+// its force pass 469 -> 452 with the line at 2^16 instead of 2^18; 250,000 uniform
+// particles lose 4 us of 56).
 constexpr int kCellidPer = 4;
-constexpr int64_t kCellidSmall = 1 << 18;
+constexpr int64_t kCellidSmall = 1 << 16;
 
 __device__ __forceinline__ int particle_cell(const Batch &B, int i, int *status)
 {

@@ -8,17 +8,20 @@
 //     sorted order, so the source list is at most 18 contiguous pieces (a row
 //     splits in two where it wraps around a periodic face; in split
 //     coordinates each neighbour cell is a piece of its own);
-//   - sources are staged through LDS in tiles of kTile with their periodic
-//     image shift applied, then read back by broadcast;
+//   - sources pass by in windows of 64 (sr_item.h) with their periodic image
+//     shift applied; those that reach the box of the item's targets are staged
+//     in LDS and read back by broadcast;
 //   - when a cell holds few targets the 64 lanes are split into S groups that
-//     take disjoint slices of a tile, and the groups' sums are added in a
+//     take the staged sources in turn, and the groups' sums are added in a
 //     fixed order through LDS at the end;
+//   - the targets of dense cells are put in Morton order first (sub_order), so
+//     that an item's targets fill a small part of the cell;
 //   - a lane may hold two targets, so that every source it reads serves both:
 //     an item takes whichever of one or two targets per lane leaves fewer
 //     lanes idle (up to 128 targets per item);
 //   - the pair loop is plain float32 VALU: one reciprocal square root,
-//     the polynomial in registers, the cutoff as a select (Sec. 3.1 describes
-//     the same select-based filtering inside the force loop).
+//     the polynomial in registers, the cutoff as a mask on the accumulation
+//     (Sec. 3.1 describes select-based filtering inside the force loop).
 // Periodic images are made exact: a target in the last cell layer of an axis
 // works in a frame shifted by -L there, so every image shift is 0 or -L and is
 // only ever applied to coordinates >= L/2, where subtracting L is exact.
