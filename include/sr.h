@@ -166,7 +166,7 @@ int sr_permute(sr_ctx *ctx, const int32_t *perm, int64_t n, int32_t elem_bytes, 
  *                   reduced in FP64 on the device in a fixed order (a Newton's
  *                   third law check; ~0 in a periodic box).
  * Arithmetic is float32 (one reciprocal square root per pair); each
- * target's sum is formed in runs of at most 128 sources whose partial sums
+ * target's sum is formed in runs of at most 640 sources whose partial sums
  * are then added, and the result is deterministic (no floating-point atomics,
  * fixed order).  Errors: SR_EINVAL, SR_ENOMEM synchronously; SR_ERANGE from
  * sr_sync. */

@@ -25,7 +25,9 @@ namespace {
 
 constexpr int kWindow = 64;          // sources tested at a time
 constexpr int kStage = 2 * kWindow;  // tile: what a pass leaves (< kWindow) and one window
-constexpr int kSumTile = 64;         // a lane's partial sums close at this many sources
+constexpr int kSumTile = 64;         // a lane's partial sums close at this many sources,
+constexpr int kSumTileLong = 512;    // ... and at this many in items of
+constexpr int kLongItem = 1 << 14;   // more stencil sources than this
 
 // The non-empty source pieces of an item's cell: piece k holds the stencil's
 // sources [beg[k], beg[k + 1]), source g of it sits in sorted slot g +
@@ -174,6 +176,7 @@ __device__ __forceinline__ void item_sources(int S, int part, int g0, int g1, bo
 {
     const TargetBox tb = target_box(L.xi, L.yi, L.zi, L.xj, L.yj, L.zj);
     const int quantum = 2 * S, qrecip = kItemTab.srecip[S];
+    const int close = g1 - g0 > kLongItem ? kSumTileLong : kSumTile;
     int fill = 0, summed = 0, p = 0;
     float4 v = load_window(sh.st, sorted, g0, g1, lane, p);
     for (int g = g0; g < g1; g += kWindow) {
@@ -217,10 +220,12 @@ __device__ __forceinline__ void item_sources(int S, int part, int g0, int g1, bo
             if (lane < fill)
                 sh.tile[lane] = r;
         }
-        // Sub-ordered sources come from one side at a time, so long partial sums
-        // grow before they cancel: closed at 256 sources the error against 64
-        // bits of a ragged halo box is 1.3e-7, at 64 it is 9e-8.
-        if (summed >= kSumTile) {
+        // A sum of N sources in runs of k rounds over k additions and over N / k:
+        // k stays near the root of N.  Error against 64 bits: a ragged halo box
+        // (a few thousand sources per sub-item) 9.1e-8 with runs of 64, 1.3e-7
+        // with 256; the 256^3 share (1e4 to 1e6 per item) 3.8e-7 with 64, 2.4e-7
+        // with 256, 2.0e-7 with 512.
+        if (summed >= close) {
             summed = 0;
             flush_sums(sh, lane, L);
         }
