@@ -23,8 +23,6 @@
 
 namespace {
 
-constexpr int kWindow = 64;          // sources tested at a time
-constexpr int kStage = 2 * kWindow;  // tile: what a pass leaves (< kWindow) and one window
 constexpr int kSumTile = 64;         // a lane's partial sums close at this many sources,
 constexpr int kSumTileLong = 512;    // ... and at this many in items of
 constexpr int kLongItem = 1 << 14;   // more stencil sources than this
@@ -41,6 +39,26 @@ struct Pieces {
     PieceRec rec[kMaxPieces];
     int beg[kMaxPieces + 2];
 };
+
+// Whether the tile of S lane groups holds every entry that item_sources writes
+// or reads: before a window it keeps at most stage_hold(S) sources or what a pass
+// leaves (less than a quantum), the window adds at most kWindow, and the last
+// pass fills its last quantum up.
+constexpr bool stage_fits(int S)
+{
+    const int q = 2 * S;
+    const int kept = stage_hold(S) > q - 1 ? stage_hold(S) : q - 1;
+    return (kept + kWindow + q - 1) / q * q <= kStage;
+}
+
+constexpr bool stages_fit()
+{
+    for (int S = 1; S <= kMaxSplit; ++S)
+        if (!stage_fits(S))
+            return false;
+    return true;
+}
+static_assert(stages_fit(), "a window and the padding of a quantum fit in the tile");
 
 // acc: each lane's sums so far, added to once per partial sum, so that they
 // hold no registers through the pair loop.
@@ -175,7 +193,7 @@ __device__ __forceinline__ void item_sources(int S, int part, int g0, int g1, bo
                                              LaneTargets &L)
 {
     const TargetBox tb = target_box(L.xi, L.yi, L.zi, L.xj, L.yj, L.zj);
-    const int quantum = 2 * S, qrecip = kItemTab.srecip[S];
+    const int quantum = 2 * S, qrecip = kItemTab.srecip[S], hold = kItemTab.hold[S];
     const int close = g1 - g0 > kLongItem ? kSumTileLong : kSumTile;
     int fill = 0, summed = 0, p = 0;
     float4 v = load_window(sh.st, sorted, g0, g1, lane, p);
@@ -196,11 +214,11 @@ __device__ __forceinline__ void item_sources(int S, int part, int g0, int g1, bo
         const bool last = g + kWindow >= g1;
         if (!last) {
             v = load_window(sh.st, sorted, g + kWindow, g1, lane, p);
-            if (fill <= kStage - kWindow)
+            if (fill <= hold)
                 continue;
         }
         // whole quanta: at the end the last one is filled up with far, massless
-        // sources (fill < kStage: as many as a quantum fit)
+        // sources, fewer than a quantum, within the tile (stage_fits)
         int n = (fill * qrecip) >> 16;
         if (last && n * quantum < fill) {
             ++n;

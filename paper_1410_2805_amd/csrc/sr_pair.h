@@ -266,13 +266,27 @@ __device__ __forceinline__ bool source_kept(const float4 &s, const TargetBox &b,
 // multiple of the slice quantum 4 S) and the quantum's 16-bit fixed-point
 // reciprocal qrecip[S], rounded up, for quanta_of; srecip[S] = ceil(2^16 /
 // (2 S)), with which n srecip / 2^16 rounds n / (2 S) down for n < 2048 (it
-// exceeds the quotient by less than n / 2^16 < 1 / 32); per target count ln
-// (1..64) of a group, lnrecip[ln] = ceil(2^16 / ln), for lane_group.  Read
-// with a uniform index, so from scalar memory instead of dividing.
+// exceeds the quotient by less than n / 2^16 < 1 / 32), and hold[S], the sources
+// a window tile may keep when another window is to follow (stage_hold); per
+// target count ln (1..64) of a group, lnrecip[ln] = ceil(2^16 / ln), for
+// lane_group.  Read with a uniform index, so from scalar memory instead of
+// dividing.
+constexpr int kWindow = 64;          // sources of an item that are tested at a time
+constexpr int kStage = 2 * kWindow;  // entries of the window tile (sr_item.h)
+
+// The whole quanta of 2 S sources that fit in the window tile, less one window:
+// a tile that keeps no more than these has room for a window and for the
+// padding of its last quantum.
+constexpr int stage_hold(int S)
+{
+    return kStage / (2 * S) * (2 * S) - kWindow;
+}
+
 struct ItemTables {
     int cap[kMaxSplit + 1];
     int qrecip[kMaxSplit + 1];
     int srecip[kMaxSplit + 1];
+    int hold[kMaxSplit + 1];
     int lnrecip[65];
 };
 
@@ -284,6 +298,7 @@ constexpr ItemTables make_item_tables()
         t.cap[s] = kTile / q * q;
         t.qrecip[s] = (65536 + q - 1) / q;
         t.srecip[s] = (65536 + 2 * s - 1) / (2 * s);
+        t.hold[s] = stage_hold(s);
     }
     for (int l = 1; l <= 64; ++l)
         t.lnrecip[l] = (65536 + l - 1) / l;
