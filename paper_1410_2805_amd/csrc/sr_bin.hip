@@ -363,13 +363,17 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int *__restrict__ cid,
 // periodic: masked passes run in split coordinates) reaches a cell with an
 // active particle (tcount, left by k_cellid); the counts of the others are set
 // to zero before the scan, so those cells stay empty.  The cells a target's
-// stencil reaches are all binned, in the order a full pass gives them, so the
-// sums are those of the full pass.
+// stencil reaches are all binned, in the order a full pass gives them.  Also
+// sets *partial (cleared before) when some particle is inactive.
 __global__ __launch_bounds__(kBlock) void k_relevant(Geom g, const int *__restrict__ tcount,
-                                                     int *__restrict__ count)
+                                                     int *__restrict__ count,
+                                                     int *__restrict__ partial)
 {
     const int c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= g.ncell || count[c] == 0)
+    const int held = c < g.ncell ? count[c] : 0;
+    if (__any(held > 0 && tcount[c] < held) && (threadIdx.x & 63) == 0)
+        *partial = 1;
+    if (held == 0)
         return;
     const int cz = div_by(c, g.div_m[0], g.div_s[0]);
     const int rem = c - cz * g.nc[0] * g.nc[1];
@@ -1162,6 +1166,7 @@ void bin_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, BinScratch &s)
     s.n_items = s.counters ? s.counters + 1 : nullptr;
     s.n_heads = s.counters ? s.counters + 2 : nullptr;
     s.n_segs = s.counters ? s.counters + 3 : nullptr;
+    s.partial = s.counters ? s.counters + 4 : nullptr;
     s.vtmp = s.ktmp = s.hist = s.hist_part = nullptr;
     if (ntot >= kRadixMinN) {
         const int64_t m = (int64_t)kRadixBins * ((ntot + kRadixTile - 1) / kRadixTile);
@@ -1272,7 +1277,7 @@ int bin_enqueue(sr_ctx *ctx, const Batch &B, const BinScratch &s, int *offsets, 
             return rc;
         if (masked) {
             hipLaunchKernelGGL(k_relevant, dim3(blocks_for(B.ctot, kBlock)), dim3(kBlock), 0,
-                               ctx->stream, B.one.g, tcount, s.count);
+                               ctx->stream, B.one.g, tcount, s.count, s.partial);
             if ((rc = sr_check_launch(ctx, "k_relevant")))
                 return rc;
         }

@@ -255,7 +255,8 @@ template <int kItemCells, int kT>
 __global__ __launch_bounds__(kT) void k_items(Batch B, const int *__restrict__ offsets,
                                                const int *__restrict__ cell_src,
                                                const unsigned long long *__restrict__ work,
-                                               const int *__restrict__ tcount, int split,
+                                               const int *__restrict__ tcount,
+                                               const int *__restrict__ partial, int split,
                                                int4 *__restrict__ items,
                                                int *__restrict__ item_cost,
                                                int *__restrict__ n_items,
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(kT) void k_items(Batch B, const int *__restrict__ o
             box = find_box(B.cstart, B.nb, c);
             src = cell_src[c];
             if (split && (tcount || box_splits(box_at(B, box).n)))
-                ns = cell_cut(len, src, work[box], &full);
+                ns = cell_cut(len, src, item_pairs(work[box], tcount && *partial), &full);
             q = mesh_chunks(len, full);
         }
         const int nseg = len > kChunk2 ? (len + kSegLen - 1) / kSegLen : 0;
@@ -790,7 +791,8 @@ static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s,
     const bool many = B.ctot >= kManyCells;
     const int cells = many ? 256 : 64;
     const auto kern = many ? k_items<256, 256> : k_items<64, 1024>;
-    hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(many ? 256 : 1024), 0, ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount,
+    hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(many ? 256 : 1024), 0,
+                       ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount, s.bin.partial,
                        s.part != nullptr ? 1 : 0, s.items, s.item_cost, s.bin.n_items, s.heads,
                        s.bin.n_heads, s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp),
                        s.bin.n_segs);

@@ -187,6 +187,7 @@ struct BinScratch {
     int *n_items;     // force work items appended by k_items
     int *n_heads;     // chunks cut into sub-items, appended by k_items
     int *n_segs;      // slot segments to be sub-ordered, appended by k_items (their list: tmp)
+    int *partial;     // 1 when a masked pass leaves some particle inactive
     unsigned long long *work;  // [nb] target-source pairs of boxes that cut their chunks
     // radix-sort binning (passes of many particles; null otherwise)
     int *vtmp;        // [ntot] index ping-pong buffer
@@ -224,7 +225,7 @@ constexpr int kChunk = 64;         // maximum targets per work item at one targe
 constexpr int kChunk2 = 128;       // ... and at two targets per lane (chaining-mesh pass)
 constexpr int kMaxSplit = 16;      // at most 16 lane groups share one target
 constexpr int kLptBlock = 1024;    // items per block of the cost-bucket sort
-constexpr int kCounters = 4;
+constexpr int kCounters = 5;
 
 // Looks up the device address of sr_force_static's fixed scratch array on
 // `device` (current) once (sr_noalloc.hip).
@@ -456,20 +457,37 @@ __host__ __device__ inline bool box_splits(int64_t n)
     return n <= kSplitMaxN;
 }
 
-// How a cell of len targets with src stencil sources each is cut in a box of
-// `work` target-source pairs that cuts its chunks: items of about work / 32768
-// pairs, i.e. four for each of the 8192 wavefronts that run at once, so that
-// the longest item stays a small part of the pass; at least kItemPairs, below
-// which an item's own work (stencil, box, output: some 2000 instructions)
-// outweighs its pairs, and at most 2^18.  A property of the box alone.  Chunks
-// of kChunk2 targets are halved, twice at most, where kMaxSrcSplit sub-items
-// are not enough.  Returns the sub-items per chunk.
+// Target-source pairs of an item, about, in a box of `work` pairs that cuts its
+// chunks: work / 16384, i.e. two items for each of the 8192 wavefronts that run
+// at once, so that the longest item stays a small part of the pass; at most
+// kItemPairsMost, and at least kItemPairs, below which an item's own work
+// (stencil, box, output: some 2000 instructions) outweighs its pairs where
+// several boxes or calls fill the GPU together (a batch of small boxes is 16 %
+// slower with 2^13).  A property of the box alone.
+//
+// A masked pass in which some particle is inactive (partial) is alone on the GPU
+// and has few targets: its items go down to kPartialPairs, or it lasts as long as
+// one item.  Multilevel step of a Zel'dovich box of 128^3 particles (displacement
+// 4 cells rms, 1..3 kicks): 2955 us with chunks of 32 targets and 4096 sources in
+// the denser cells, 3020 with 2^16 here, 2730 with 2^15, 2645 with 2^14, 2^13 and
+// 2^12 (displacement 8: 4380, 4060, 3980, 3965, 3940, 3970).  A masked pass over
+// every particle cuts as a plain pass does and gives its sums bit for bit.
 constexpr long long kItemPairs = 1 << 16;
+constexpr long long kItemPairsMost = 1 << 18;
+constexpr long long kPartialPairs = 1 << 13;
 
-__device__ __forceinline__ int cell_cut(int len, int src, unsigned long long work, int *full)
+__host__ __device__ constexpr long long item_pairs(unsigned long long work, bool partial)
 {
-    long long t = (long long)(work >> 14);
-    t = t < kItemPairs ? kItemPairs : (t > (1 << 18) ? (1 << 18) : t);
+    const long long least = partial ? kPartialPairs : kItemPairs;
+    const long long t = (long long)(work >> 14);
+    return t < least ? least : (t > kItemPairsMost ? kItemPairsMost : t);
+}
+
+// How a cell of len targets with src stencil sources each is cut into items of
+// about t pairs.  Chunks of kChunk2 targets are halved, twice at most, where
+// kMaxSrcSplit sub-items are not enough.  Returns the sub-items per chunk.
+__device__ __forceinline__ int cell_cut(int len, int src, long long t, int *full)
+{
     int f = kChunk2;
     while (f > kChunk2 / 4 && (long long)src * (len < f ? len : f) > kMaxSrcSplit * t)
         f >>= 1;
