@@ -143,8 +143,8 @@ __global__ __launch_bounds__(64, 8) void k_force_persistent(Batch B, const int4 
     }
 }
 
-// Useful-pair and candidate counts with the same stencil and cutoff test
-// (one box).
+// Useful-pair and candidate counts with the same stencil, chunks and cutoff
+// test (one box; a chunk's sub-items, which share its target box, count as one).
 __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restrict__ items,
                                                    const int *__restrict__ n_items,
                                                    const float4 *__restrict__ sorted,
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 }
 
 // Work items of a block of kItemCells cells: each of the first kItemCells
-// threads takes one cell's chunk and sub-item counts (with split, the chunks of
+// threads takes one cell's chunk and sub-item counts (split: the chunks of
 // boxes that box_splits admits, and of any box in masked passes, are cut by
 // cell_cut; with target counts, a masked pass, the chunks cover the cell's
 // first tcount[c] slots, where its active particles sit), the block
@@ -248,6 +248,10 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // the cells of a halo's core, with thousands of sub-items, sit in one block (that
 // box 460 us with 1024, 469 with 256; an 80^3 halo box 1955 and 1988).
 constexpr int kManyCells = 32768;
+// What k_items cuts: kCutNone whole chunks only, kCutSub chunks and sub-items,
+// kCutChunks the same chunks as one item each (sr_pair_stats: the force pass's
+// target boxes, with every source counted once).
+constexpr int kCutNone = 0, kCutSub = 1, kCutChunks = 2;
 constexpr int kSegThreads = 512;  // threads that order a segment
 constexpr int kSegRounds = 8;     // slots per thread
 constexpr int kSegLen = kSegThreads * kSegRounds;
@@ -284,8 +288,10 @@ __global__ __launch_bounds__(kT) void k_items(Batch B, const int *__restrict__ o
         if (len > 0) {
             box = find_box(B.cstart, B.nb, c);
             src = cell_src[c];
-            if (split && (tcount || box_splits(box_at(B, box).n)))
+            if (split != kCutNone && (tcount || box_splits(box_at(B, box).n)))
                 ns = cell_cut(len, src, item_pairs(work[box], tcount && *partial), &full);
+            if (split == kCutChunks)
+                ns = 1;
             q = mesh_chunks(len, full);
         }
         const int nseg = len > kChunk2 ? (len + kSegLen - 1) / kSegLen : 0;
@@ -783,7 +789,8 @@ int lpt_sort_enqueue(sr_ctx *ctx, const int4 *items, const int *item_cost, const
 
 // Binning with the per-cell item counts, the work items, then the
 // longest-first order when asked for.
-static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s, int order)
+static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s, int order,
+                             int split)
 {
     int rc;
     if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, s.tcount, true)))
@@ -793,9 +800,8 @@ static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s,
     const auto kern = many ? k_items<256, 256> : k_items<64, 1024>;
     hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(many ? 256 : 1024), 0,
                        ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount, s.bin.partial,
-                       s.part != nullptr ? 1 : 0, s.items, s.item_cost, s.bin.n_items, s.heads,
-                       s.bin.n_heads, s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp),
-                       s.bin.n_segs);
+                       split, s.items, s.item_cost, s.bin.n_items, s.heads, s.bin.n_heads,
+                       s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp), s.bin.n_segs);
     if ((rc = sr_check_launch(ctx, "k_items")))
         return rc;
     const int nseg = sub_order_blocks(B.ntot);
@@ -814,7 +820,7 @@ int force_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s, const Forc
 {
     int rc;
     sr_timing_mark(ctx, rec, 0);
-    if ((rc = bin_items_enqueue(ctx, B, s, order)))
+    if ((rc = bin_items_enqueue(ctx, B, s, order, s.part != nullptr ? kCutSub : kCutNone)))
         return rc;
     sr_timing_mark(ctx, rec, 1);
     const int4 *items = order == 1 ? s.items_lpt : s.items;
@@ -1040,12 +1046,12 @@ extern "C" int sr_pair_stats(sr_ctx *ctx, const float *x, const float *y, const 
         return sr_fail(ctx, SR_EDEVICE, "hipSetDevice failed");
     Bump sz{nullptr, 0, 0};
     ForceScratch s;
-    force_layout(sz, n, B.ctot, 1, s, false, false);  // whole chunks
+    force_layout(sz, n, B.ctot, 1, s, false, false);  // no sub-items
     if ((rc = sr_arena_reserve(ctx, sz.off)))
         return rc;
     Bump b{ctx->arena, 0, ctx->arena_cap};
     force_layout(b, n, B.ctot, 1, s, false, false);
-    if ((rc = bin_items_enqueue(ctx, B, s, 0)))
+    if ((rc = bin_items_enqueue(ctx, B, s, 0, kCutChunks)))
         return rc;
     // eps = 0 so that se = s and the test is s < r_max^2
     ForceParams fp = make_params(r_max, 0.0f, zero_poly);
