@@ -62,7 +62,7 @@ __global__ __launch_bounds__(64, 8) void k_force(Batch B, const int4 *__restrict
                                                  const int *__restrict__ offsets,
                                                  const int *__restrict__ perm,
                                                  const int *__restrict__ mass_mixed, ForceParams fp,
-                                                 float4 *__restrict__ subsums)
+                                                 float *__restrict__ subsums)
 {
     __shared__ ItemShared sh;
     const int n = *n_items;
@@ -72,40 +72,40 @@ __global__ __launch_bounds__(64, 8) void k_force(Batch B, const int4 *__restrict
 }
 
 // Adds the partial sums of the sub-items of every chunk cut into sub-items
-// (heads: each chunk's first sub-item), in sub-item order -- sub-item 0's
-// sums are in the outputs already -- and writes the chunk's accelerations
-// (passive targets' partials are exact zeros).  One wavefront per head
-// (grid-stride), two targets per lane at most.  Latency-bound: the planes of a
-// target are all loaded before the first is added.
+// (heads: each chunk's first sub-item), in sub-item order, and writes the chunk's
+// accelerations (passive targets' partials are exact zeros).  One wavefront per
+// head (grid-stride), two targets per lane at most.  Latency-bound: the sums of a
+// target are all loaded before the first is added; its only scattered accesses
+// are the three it writes.
 __global__ __launch_bounds__(256) void k_subsum(Batch B, const int4 *__restrict__ heads,
                                                 const int *__restrict__ n_heads,
                                                 const int *__restrict__ perm,
-                                                const float4 *__restrict__ subsums)
+                                                const float *__restrict__ subsums)
 {
     const int n = *n_heads, lane = threadIdx.x & 63;
     for (int h = blockIdx.x * 4 + (threadIdx.x >> 6); h < n; h += gridDim.x * 4) {
         const int4 item = heads[h];
-        const int ns = item_nsub(item);
+        const int ns = __builtin_amdgcn_readfirstlane(item_nsub(item));
         const BoxDesc &d = box_at(B, item_box(item));
         for (int t = lane; t < item.z; t += 64) {
             const int slot = item.y + t;
-            float4 v[kMaxSrcSplit - 1];
+            float v[kMaxSrcSplit][3];
 #pragma unroll
-            for (int k = 0; k < kMaxSrcSplit - 1; ++k)
-                v[k] = k < ns - 1 ? subsums[(size_t)k * B.ntot + slot]
-                                  : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int k = 0; k < kMaxSrcSplit; ++k)
+                if (k < ns)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        v[k][c] = subsums[subsum_at(k, c, B.ntot, slot)];
             const int orig = perm[slot] - d.pbase;
-            float ax = d.ax[orig], ay = d.ay[orig], az = d.az[orig];
 #pragma unroll
-            for (int k = 0; k < kMaxSrcSplit - 1; ++k)
-                if (k < ns - 1) {
-                    ax += v[k].x;
-                    ay += v[k].y;
-                    az += v[k].z;
-                }
-            d.ax[orig] = ax;
-            d.ay[orig] = ay;
-            d.az[orig] = az;
+            for (int k = 1; k < kMaxSrcSplit; ++k)
+                if (k < ns)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        v[0][c] += v[k][c];
+            d.ax[orig] = v[0][0];
+            d.ay[orig] = v[0][1];
+            d.az[orig] = v[0][2];
         }
     }
 }
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64, 8) void k_force_persistent(Batch B, const int4 
                                                             const int *__restrict__ mass_mixed,
                                                             ForceParams fp,
                                                             int *__restrict__ queue,
-                                                            float4 *__restrict__ subsums)
+                                                            float *__restrict__ subsums)
 {
     __shared__ ItemShared sh;
     __shared__ int next;
@@ -712,7 +712,7 @@ void force_layout(Bump &b, int64_t ntot, int64_t ctot, int nb, ForceScratch &s, 
     s.items_lpt = b.take<int4>((size_t)ub);
     s.queue = b.take<int>(1);
     s.mom_part = b.take<double>((size_t)(nb > 0 ? nb : 1) * kRedBlocks * 3);
-    s.part = split ? b.take<float4>(nn * (kMaxSrcSplit - 1)) : nullptr;
+    s.part = split ? b.take<float>(nn * 4 * (kMaxSrcSplit - 1)) : nullptr;
     s.heads = split ? b.take<int4>((size_t)item_bound(ntot, ctot)) : nullptr;
     s.tcount = masked ? b.take<int>((size_t)ctot) : nullptr;
 }

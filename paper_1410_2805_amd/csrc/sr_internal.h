@@ -214,7 +214,7 @@ struct ForceScratch {
     int4 *items_lpt;  // [item bound] items by decreasing cost bucket
     int *queue;       // [1] persistent work counter
     double *mom_part; // [nb * kRedBlocks * 3]
-    float4 *part;     // [(kMaxSrcSplit - 1) * ntot] partial sums of sub-items 1.., or null
+    float *part;      // [4 (kMaxSrcSplit - 1) ntot] partial sums of sub-items (subsum_at), or null
     int4 *heads;      // [chunk bound] first sub-items of the chunks cut into sub-items
     int *tcount;      // [ctot] active targets per cell (masked passes), or null
 };

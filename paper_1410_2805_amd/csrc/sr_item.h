@@ -272,16 +272,30 @@ __device__ __forceinline__ ItemLane item_lane(bool two, int nt, int S, int lane)
     return T;
 }
 
-// Stores the acceleration of the target in a sorted slot: sub-item 0 writes it
-// as a whole item does, sub-item sub > 0 its partial sums to plane sub - 1.
+// Where sub-item sk of a chunk leaves component c of the sum of the target in a
+// sorted slot, among the partial sums of all sub-items (s.part).
+__device__ __forceinline__ size_t subsum_at(int sk, int c, int ntot, int slot)
+{
+    return (size_t)(3 * sk + c) * ntot + slot;
+}
+static_assert(3 * kMaxSrcSplit <= 4 * (kMaxSrcSplit - 1), "s.part holds every sub-item's sums");
+
+// Stores the acceleration of the target in a sorted slot: a whole item writes it
+// out, a sub-item leaves its partial sums for k_subsum, in slot order (with
+// sub-item 0's sums written out and read back scattered, and 16 bytes per sum, a
+// pass over 32 halo boxes of 16^3..96^3 particles took 11204 us here and 312 in
+// k_subsum instead of 10952 and 236).
 __device__ __forceinline__ void write_target(const BoxDesc &d, const int *__restrict__ perm,
-                                             float4 *__restrict__ subsums, int ntot, int sub,
-                                             int slot, bool passive, float ax, float ay, float az)
+                                             float *__restrict__ subsums, int ntot, bool cut,
+                                             int sub, int slot, bool passive, float ax, float ay,
+                                             float az)
 {
     if (passive)
         ax = ay = az = 0.f;
-    if (sub > 0) {
-        subsums[(size_t)(sub - 1) * ntot + slot] = make_float4(ax, ay, az, 0.f);
+    if (cut) {
+        subsums[subsum_at(sub, 0, ntot, slot)] = ax;
+        subsums[subsum_at(sub, 1, ntot, slot)] = ay;
+        subsums[subsum_at(sub, 2, ntot, slot)] = az;
     } else {
         const int orig = perm[slot] - d.pbase;
         d.ax[orig] = ax;
@@ -297,7 +311,7 @@ __device__ __forceinline__ void process_item(const Batch &B, const int4 item,
                                              const int *__restrict__ perm,
                                              const int *__restrict__ mass_mixed,
                                              const ForceParams &fp, ItemShared &sh, int lane,
-                                             float4 *__restrict__ subsums)
+                                             float *__restrict__ subsums)
 {
     const int kb = item.y, nt = item.z, S = item_split(item), box = item_box(item);
     const BoxDesc &d = box_at(B, box);
@@ -360,11 +374,12 @@ __device__ __forceinline__ void process_item(const Batch &B, const int4 item,
             for (int k = 0; k < 6; ++k)
                 a[k] += sh.acc[k][lane + q * T.ln];
         const float m = uniform ? pt.w : 1.f, m2 = uniform ? pt2.w : 1.f;
-        write_target(d, perm, subsums, B.ntot, item_sub(item), kb + T.t, is_passive(pt, g),
+        const bool cut = item_nsub(item) > 1;
+        write_target(d, perm, subsums, B.ntot, cut, item_sub(item), kb + T.t, is_passive(pt, g),
                      a[0] * m, a[1] * m, a[2] * m);
         if (T.has2)
-            write_target(d, perm, subsums, B.ntot, item_sub(item), kb + T.t2, is_passive(pt2, g),
-                         a[3] * m2, a[4] * m2, a[5] * m2);
+            write_target(d, perm, subsums, B.ntot, cut, item_sub(item), kb + T.t2,
+                         is_passive(pt2, g), a[3] * m2, a[4] * m2, a[5] * m2);
     }
     __syncthreads();  // the next item replaces the pieces and the sums
 }
