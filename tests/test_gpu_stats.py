@@ -1,8 +1,8 @@
 """sr_pair_stats against a count of the force pass's work items by hand: two cells
 of a few thousand particles that meet at a corner, in a periodic box, whose chunks
-the force pass halves to 64 or 32 targets.  The slots in sub-order, the chunks, their targets' boxes and
-the sources within the cutoff of each box are formed in numpy (float32 where the
-kernels use it), so the candidates are equal, not close."""
+the force pass halves to 64 or 32 targets.  The slots in sub-order, the chunks,
+their targets' boxes and the sources within the cutoff of each box are formed in
+numpy (float32 where the kernels use it)."""
 import numpy as np
 import pytest
 
