@@ -16,8 +16,10 @@
 //              wavefront (registers, or a wavefront-private LDS bitonic
 //              sort); larger cells go to k_segsort_large (one block,
 //              LDS-sorted runs merged by rank).  The pass writes the inverse
-//              permutation and, for the force pass, the work items per cell.
-//   k_gather   the sorted float4 (x, y, z, m) copy, through the inverse.
+//              permutation.
+//   k_gather   the sorted float4 (x, y, z, m) copy, through the inverse; for the
+//              force pass also each cell's stencil sources and each box's
+//              target-source pairs.
 // All kernels work on a batch of boxes whose particles and cells are numbered
 // consecutively; one box is a batch of one.  Passes of 2^22 particles or
 // more without an activity mask take a stable LSD radix sort of the cell ids
@@ -85,12 +87,16 @@ __global__ void k_fill(int *__restrict__ p, int value, int64_t count)
         p[i] = value;
 }
 
-// Particles per thread of the histogram pass: one up to kCellidSmall particles
-// (a block of 1024 then serializes four rounds on one CU while others idle:
-// 32,768 particles 13.6 us at four per thread), else four: clustered input then
-// adds fewer atomics to the same cells (a halo box of 154003 particles 27 -> 18 us,
-// its force pass 469 -> 452 with the line at 2^16 instead of 2^18; 250,000 uniform
-// particles lose 4 us of 56).
+// Particles per thread of the histogram pass.  Four let a block add up more
+// particles of a cell before its one atomic per cell, which pays where many
+// particles share cells; one spreads a small pass over four times the blocks,
+// which pays while blocks of 1024 particles leave CUs idle (up to 2^18 particles,
+// 256 blocks).  What a given box wants depends on its clustering, which is not
+// known before the pass; the line is by the count alone, where the gain on even
+// input still covers the loss on clustered input: 32,768 uniform particles 13.6
+// us at four per thread; with one, a halo box of 154003 particles took 27 us
+// instead of 18 (its force pass 469 instead of 452) and 250,000 uniform particles
+// 52 instead of 56.
 constexpr int kCellidPer = 4;
 constexpr int64_t kCellidSmall = 1 << 16;
 

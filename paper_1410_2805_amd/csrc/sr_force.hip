@@ -448,10 +448,12 @@ __global__ __launch_bounds__(256) void k_lpt_scatter(const int4 *__restrict__ it
 // each one's targets then fill a small part of the cell, and fewer sources pass
 // the test against their box (on the 256^3 clustered share 9570 candidates per
 // target instead of 10549 in input order, by a CPU model; 9670 with quarters).
-// The order depends on the cell's targets alone, so every pass that bins the
-// same cell sums it the same way.  k_force on that share 64.1 -> 57.9 ms, on an
-// 80^3 halo box 1.99 -> 1.89 ms.  Cells of at most kChunk2 targets are one item
-// or few small ones, and stay as they are.
+// The order depends on the cell's targets alone, so a box gives the same bits
+// alone and in a batch.  A masked pass orders the active particles, the front of
+// each cell, only: it agrees bitwise with a plain pass when every particle is
+// active, else to float32 summation order.  k_force on that share 64.1 -> 57.9
+// ms, on an 80^3 halo box 1.99 -> 1.89 ms.  Cells of at most kChunk2 targets are
+// one item or few small ones, and stay as they are.
 //
 // Latency bounds it on small boxes (14 us with 16 slots per thread and 256
 // threads on a halo box of 154003 particles, 5 us of them the launch and the item
@@ -590,13 +592,11 @@ __device__ void sub_order(SegShared &S, float4 *__restrict__ sorted, int *__rest
 
 // One launch: the first nseg blocks sub-order the segments in turn, the others
 // put the items in longest-first order.
-__global__ __launch_bounds__(kSegThreads) void k_order(const int2 *__restrict__ segs,
-                                               const int *__restrict__ n_segs, int nseg,
-                                               float4 *__restrict__ sorted, int *__restrict__ perm,
-                                               const int4 *__restrict__ items,
-                                               const int *__restrict__ item_cost,
-                                               const int *__restrict__ n_items,
-                                               int *__restrict__ lpt, int4 *__restrict__ out)
+__global__ __launch_bounds__(kSegThreads) void k_order(
+    const int2 *__restrict__ segs, const int *__restrict__ n_segs, int nseg,
+    float4 *__restrict__ sorted, int *__restrict__ perm, const int4 *__restrict__ items,
+    const int *__restrict__ item_cost, const int *__restrict__ n_items, int *__restrict__ lpt,
+    int4 *__restrict__ out)
 {
     __shared__ SegShared S;
     if ((int)blockIdx.x >= nseg) {
@@ -782,8 +782,8 @@ ForceParams make_params(float r_max, float eps, const float *poly)
 int lpt_sort_enqueue(sr_ctx *ctx, const int4 *items, const int *item_cost, const int *n_items,
                      int64_t bound, int *lpt, int4 *out)
 {
-    hipLaunchKernelGGL(k_lpt_scatter, dim3(lpt_blocks(bound)), dim3(256), 0, ctx->stream, items, item_cost,
-                       n_items, lpt, out);
+    hipLaunchKernelGGL(k_lpt_scatter, dim3(lpt_blocks(bound)), dim3(256), 0, ctx->stream, items,
+                       item_cost, n_items, lpt, out);
     return sr_check_launch(ctx, "k_lpt");
 }
 

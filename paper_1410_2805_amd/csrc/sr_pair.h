@@ -40,9 +40,9 @@ __device__ __forceinline__ int wave_exclusive_scan(int v, int lane, int *total)
 // 9 (2 hx + 1) each own one cell of the stencil and the shift is the cell's
 // offset from the target cell, (dx w0, dy w1, dz w2), so coordinates stay
 // cell-relative and periodic wrap needs no shift at all.
-__device__ __forceinline__ void stencil_piece(const int *__restrict__ offsets, const Geom &g, int cx,
-                                              int cy, int cz, const float F[3], int lane, int &src,
-                                              int &len, float &sx, float &sy, float &sz)
+__device__ __forceinline__ void stencil_piece(const int *__restrict__ offsets, const Geom &g,
+                                              int cx, int cy, int cz, const float F[3], int lane,
+                                              int &src, int &len, float &sx, float &sy, float &sz)
 {
     len = src = 0;
     sx = sy = sz = 0.f;
