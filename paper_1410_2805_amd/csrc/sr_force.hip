@@ -241,13 +241,16 @@ __global__ __launch_bounds__(64) void k_pair_stats(Batch B, const int4 *__restri
 // kChunk2 targets are appended to segs, in segments of at most kSegLen, for
 // sub_order.
 //
-// The atomics on the counters bound it where there are many blocks, the longest
-// block where there are few: passes of kManyCells cells or more take 256 cells
-// per block (128^3 lattice, 79507 cells: the pass 585 us with 64, 574 with 256),
-// others 64 (a halo box of 154003 particles 468 against 475 us), by 1024 threads:
-// the cells of a halo's core, with thousands of sub-items, sit in one block (that
-// box 460 us with 1024, 469 with 256; an 80^3 halo box 1955 and 1988).
+// The atomics on the counters (one address, 12 ns each) bound it where there are
+// many blocks, the longest block where there are few: passes of kMostCells cells or
+// more take 1024 cells per block (100000 particles in 128^3 cells: 100 us with 256,
+// 30 with 1024), of kManyCells or more 256 (128^3 lattice, 79507 cells: the pass 585
+// us with 64, 574 with 256), others 64 (a halo box of 154003 particles 468 against
+// 475 us), by 1024 threads: the cells of a halo's core, with thousands of sub-items,
+// sit in one block (that box 460 us with 1024, 469 with 256; an 80^3 halo box 1955
+// and 1988).
 constexpr int kManyCells = 32768;
+constexpr int kMostCells = 1 << 18;
 // What k_items cuts: kCutNone whole chunks only, kCutSub chunks and sub-items,
 // kCutChunks the same chunks as one item each (sr_pair_stats: the force pass's
 // target boxes, with every source counted once).
@@ -269,6 +272,7 @@ __global__ __launch_bounds__(kT) void k_items(Batch B, const int *__restrict__ o
                                                int *__restrict__ lpt, int2 *__restrict__ segs,
                                                int *__restrict__ n_segs)
 {
+    static_assert(kT >= kItemCells, "one cell per thread");
     constexpr int kItemWaves = kItemCells / 64;
     __shared__ int base, sbase;
     __shared__ int s_wave[kItemWaves], s_wseg[kItemWaves];  // items and segments per wavefront
@@ -795,10 +799,10 @@ static int bin_items_enqueue(sr_ctx *ctx, const Batch &B, const ForceScratch &s,
     int rc;
     if ((rc = bin_enqueue(ctx, B, s.bin, s.offsets, s.perm, s.sorted, s.tcount, true)))
         return rc;
-    const bool many = B.ctot >= kManyCells;
-    const int cells = many ? 256 : 64;
-    const auto kern = many ? k_items<256, 256> : k_items<64, 1024>;
-    hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(many ? 256 : 1024), 0,
+    const bool most = B.ctot >= kMostCells, many = B.ctot >= kManyCells;
+    const int cells = most ? 1024 : (many ? 256 : 64), threads = many && !most ? 256 : 1024;
+    const auto kern = most ? k_items<1024, 1024> : (many ? k_items<256, 256> : k_items<64, 1024>);
+    hipLaunchKernelGGL(kern, dim3((B.ctot + cells - 1) / cells), dim3(threads), 0,
                        ctx->stream, B, s.offsets, s.bin.count, s.bin.work, s.tcount, s.bin.partial,
                        split, s.items, s.item_cost, s.bin.n_items, s.heads, s.bin.n_heads,
                        s.bin.lpt, reinterpret_cast<int2 *>(s.bin.tmp), s.bin.n_segs);
